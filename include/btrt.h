@@ -157,9 +157,11 @@ typedef struct {
     double K2[4];                     /* resolved K2 */
     double k0;
     size_t workspace_bytes;           /* device bytes a handle needs */
-    double bytes_per_node_launch;     /* algorithmic HBM bytes per node and sweep launch: the
-                                         state read once and written once (9 populations +
-                                         phi each way) plus a source field and an A0 field when
+    double bytes_per_node_launch;     /* algorithmic HBM bytes per node and sweep launch in the
+                                         population form: the state read once and written once
+                                         (9 populations + phi each way; with k0 = 1 and K2 = 1 in
+                                         FP64/FP32 storage the library moves phi and two or three
+                                         moments instead) plus a source field and an A0 field when
                                          given, however many steps the launch fuses */
     int64_t step;                     /* steps taken (btrt_get_info only) */
 } btrt_info_t;
@@ -230,7 +232,11 @@ int btrt_set_walls(btrt_t* h, const double* values, int64_t steps);
  *                     hold one wavefront per SIMD, take the height that fits every strip in
  *                     the resident slots at once when that is 64 rows or more);
  *                     with one step per launch, the tile height 1, 2, 4, 8 or 16 (0: 4)
- *   strips_per_group  1 or 4 strips per workgroup, walked side by side in lockstep (0: auto)
+ *                     With k0 = 1 and K2 = 1 in FP64/FP32 storage, automatic strips are cut so that
+ *                     all of a launch are resident at once (reported as the next lower of 8, 16, 32
+ *                     and 64 rows below 64), and an automatic shape of one step per launch advances
+ *                     several of the steps of one btrt_step call in each launch
+ *   strips_per_group  1 or 4 strips per workgroup, walked side by side (0: auto)
  *   tile              1 with steps_per_launch 2: the two-step LDS tile kernel instead of a
  *                     strip walker (tiles of 64 x 8 nodes in FP64, 64 x 16 otherwise) */
 typedef struct {
@@ -314,7 +320,7 @@ int btrt_get_info(const btrt_t* h, btrt_info_t* info);
 
 /* ---- checkpoint and resume -------------------------------------------------------------
  * A checkpoint holds the solver state between steps: the step count, the stored populations
- * f+(t-1) and phi(t-1) in the handle's storage format, the Eq. (64) residual snapshot, the
+ * f+(t-1) (or the moments that stand for them) and phi(t-1) in the handle's storage format, the Eq. (64) residual snapshot, the
  * Dirichlet values the next pull reads, and a copy of the problem's derived constants. It is
  * plain host memory, laid out by the library (a header, then the arrays), valid on any handle
  * of the same library build. Per-node inputs (a source field, an A0 field) are not stored: the

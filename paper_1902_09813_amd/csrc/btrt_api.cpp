@@ -76,10 +76,10 @@ void release(btrt* h)
 }
 
 // ---- checkpoint layout ---------------------------------------------------------------------
-// [header (kCkHeader bytes)] [f: 9 planes, storage format] [phi: one plane] [snapshot: nx*ny FP64]
+// [header (kCkHeader bytes)] [f: the planes of the state (9, or 2 or 3 in the moment form), storage format] [phi: one plane] [snapshot: nx*ny FP64]
 // [wall entry: one wall-table entry (Instance::wall_entry_slots() values) in the phi type,
 //  general node model only]
-constexpr char kCkMagic[8] = {'B', 'T', 'R', 'T', 'C', 'K', 'P', '2'};
+constexpr char kCkMagic[8] = {'B', 'T', 'R', 'T', 'C', 'K', 'P', '3'};
 constexpr int kCkParams = 48;
 constexpr size_t kCkHeader = 512;
 
@@ -128,7 +128,7 @@ CkSizes ck_sizes(const Instance& I)
 {
     CkSizes z{};
     const size_t ps = I.precision == BTRT_F64 ? 8 : 4;
-    z.f = 9 * static_cast<size_t>(I.plane) * pop_bytes(I.precision);
+    z.f = static_cast<size_t>(I.state_planes()) * static_cast<size_t>(I.plane) * pop_bytes(I.precision);
     z.phi = static_cast<size_t>(I.plane) * ps;
     z.snap = static_cast<size_t>(I.nx) * I.ny * 8;
     z.wall = I.gen ? static_cast<size_t>(I.wall_entry_slots()) * ps : 0;
@@ -219,11 +219,7 @@ int btrt_restore(btrt_t* h, const void* buf, size_t bytes)
     // D != phi I; the same on both sides, as the constants match) keeps its one-entry table in
     // the workspace; a checkpoint taken under a wall schedule brings the values then in force,
     // which become a one-entry table of their own (steps wait for btrt_set_walls).
-    const SweepArgs<double>& a64 = I.a64;
-    const SweepArgs<float>& a32 = I.a32;
-    const bool problem_gen = I.precision == BTRT_F64
-                                 ? (a64.fcx != 0 || a64.fcy != 0 || a64.rr != 0 || a64.dpoly)
-                                 : (a32.fcx != 0 || a32.fcy != 0 || a32.rr != 0 || a32.dpoly);
+    const bool problem_gen = I.gen_problem;
     void* wmem = nullptr;
     if (hd.wall_mode == 1) {
         if (hipMalloc(&wmem, wall) != hipSuccess) {
@@ -457,7 +453,8 @@ int btrt_tune(btrt_t* h, int64_t max_steps, btrt_launch_t* best, int64_t* steps_
         std::vector<size_t> timed;
         int rc = BTRT_OK;
         for (size_t c : list) {
-            const int64_t need = static_cast<int64_t>(1 + reps) * cand[c].steps;
+            const int span = cand[c].fuse > 0 ? cand[c].fuse : cand[c].steps;  // steps of one launch
+            const int64_t need = static_cast<int64_t>(1 + reps) * span;
             if (used + need > max_steps) continue;
             hipEvent_t e0 = nullptr, e1 = nullptr;
             if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
@@ -467,9 +464,9 @@ int btrt_tune(btrt_t* h, int64_t max_steps, btrt_launch_t* best, int64_t* steps_
             }
             ev.push_back(e0);
             ev.push_back(e1);
-            rc = enqueue_steps(h, cand[c], cand[c].steps);
+            rc = enqueue_steps(h, cand[c], span);
             if (rc == BTRT_OK && hipEventRecord(e0, h->stream) != hipSuccess) rc = fail(BTRT_E_DEVICE, "hipEventRecord");
-            if (rc == BTRT_OK) rc = enqueue_steps(h, cand[c], static_cast<int64_t>(reps) * cand[c].steps);
+            if (rc == BTRT_OK) rc = enqueue_steps(h, cand[c], static_cast<int64_t>(reps) * span);
             if (rc == BTRT_OK && hipEventRecord(e1, h->stream) != hipSuccess) rc = fail(BTRT_E_DEVICE, "hipEventRecord");
             used += need;
             timed.push_back(c);
@@ -483,7 +480,8 @@ int btrt_tune(btrt_t* h, int64_t max_steps, btrt_launch_t* best, int64_t* steps_
                 rc = fail(BTRT_E_DEVICE, "hipEventElapsedTime failed");
                 break;
             }
-            ms_per_step[timed[j]] += ms / (reps * cand[timed[j]].steps);
+            const LaunchCfg& t = cand[timed[j]];
+            ms_per_step[timed[j]] += ms / (reps * (t.fuse > 0 ? t.fuse : t.steps));
             ++n[timed[j]];
         }
         for (hipEvent_t x : ev) (void)hipEventDestroy(x);

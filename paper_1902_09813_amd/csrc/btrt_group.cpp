@@ -34,52 +34,80 @@ int grid_blocks(const Group& g) { return g.cfg.blocks_per_cu > 0 ? g.ncu * g.cfg
 constexpr int kDefaultStripRows = 16;
 int strip_rows(const btrt_batch_config_t& c) { return c.strip_rows > 0 ? c.strip_rows : kDefaultStripRows; }
 
-hipError_t raw_launch(Group& g, int steps, int flip)
+// Rows of a unit of `steps` steps: the configured strip height, or the tiles' own below four steps.
+int unit_rows(const Group& g, int p, int steps)
 {
-    const int n = static_cast<int>(g.inst.size());
-    const int rows = strip_rows(g.cfg);
-    bool k0one = true;
-    for (const Instance* I : g.inst) k0one = k0one && I->k0_one;
-    if (g.precision == BTRT_F64)
-        return btrtk::launch_batch_sweep<double>(static_cast<const BatchEntry<double>*>(g.d_ent), g.d_begin[steps],
-                                                 g.d_par, n, g.total[steps], flip, steps, grid_blocks(g), rows, k0one,
-                                                 g.nts, g.stream);
-    return btrtk::launch_batch_sweep<float>(static_cast<const BatchEntry<float>*>(g.d_ent), g.d_begin[steps], g.d_par,
-                                            n, g.total[steps], flip, steps, grid_blocks(g), rows, k0one, g.nts,
-                                            g.stream);
+    (void)p;
+    return btrtk::batch_walks(steps) ? strip_rows(g.cfg) : btrtk::tile_rows(steps, g.precision == BTRT_F64 ? 8 : 4);
 }
 
-// Offsets of each member's units in the concatenated list for `steps` per launch: 64 x rows
-// tiles (1 and 2 steps), or walker strips (batch_strip_columns(steps) x rows).
-int upload_begin(Group& g, int steps, int rows)
+// Launches one part: slot picks the unit table (steps, or 0: one step for the members that need one).
+hipError_t part_launch(Group& g, int p, int slot, int steps, int flip)
 {
-    const int n = static_cast<int>(g.inst.size());
+    const Group::Part& P = g.part[p];
+    const int n = static_cast<int>(P.inst.size());
+    const int rows = unit_rows(g, p, steps);
+    if (n == 0 || P.total[slot] == 0) return hipSuccess;
+    if (p == 1) {
+        if (g.precision == BTRT_F64)
+            return btrtk::launch_batch_mom<double>(static_cast<const BatchEntry<double>*>(P.d_ent), P.d_begin[slot], P.d_par,
+                                                   n, P.total[slot], flip, steps, grid_blocks(g), rows, g.stream);
+        return btrtk::launch_batch_mom<float>(static_cast<const BatchEntry<float>*>(P.d_ent), P.d_begin[slot], P.d_par, n,
+                                              P.total[slot], flip, steps, grid_blocks(g), rows, g.stream);
+    }
+    bool k0one = true;
+    for (const Instance* I : P.inst) k0one = k0one && I->k0_one;
+    if (g.precision == BTRT_F64)
+        return btrtk::launch_batch_sweep<double>(static_cast<const BatchEntry<double>*>(P.d_ent), P.d_begin[slot], P.d_par,
+                                                 n, P.total[slot], flip, steps, grid_blocks(g), rows, k0one, g.nts,
+                                                 g.stream);
+    return btrtk::launch_batch_sweep<float>(static_cast<const BatchEntry<float>*>(P.d_ent), P.d_begin[slot], P.d_par, n,
+                                            P.total[slot], flip, steps, grid_blocks(g), rows, k0one, g.nts, g.stream);
+}
+
+hipError_t raw_launch(Group& g, int steps, int flip)
+{
+    hipError_t e = part_launch(g, 0, steps, steps, flip);
+    return e == hipSuccess ? part_launch(g, 1, steps, steps, flip) : e;
+}
+
+// Offsets of each member's units in part p's concatenated list for `steps` per launch: 64 x rows
+// tiles, or walker strips. skip_first: members whose first step is free get no units.
+int upload_begin(Group& g, int p, int slot, int steps, int rows, bool skip_first)
+{
+    Group::Part& P = g.part[p];
+    const int n = static_cast<int>(P.inst.size());
+    if (n == 0) return BTRT_OK;
     std::vector<int> begin(n + 1);
-    const int width = btrtk::batch_walks(steps) ? btrtk::batch_strip_columns(steps) : btrtk::kTileWidth;
+    const int width = p == 1 ? btrtk::mom_strip_columns(steps)
+                             : (btrtk::batch_walks(steps) ? btrtk::batch_strip_columns(steps) : btrtk::kTileWidth);
     int64_t acc = 0;
     for (int i = 0; i < n; ++i) {
         begin[i] = static_cast<int>(acc);
-        const Instance& I = *g.inst[i];
-        acc += static_cast<int64_t>((I.nx + width - 1) / width) * ((I.ny + rows - 1) / rows);
+        const Instance& I = *P.inst[i];
+        if (!(skip_first && I.first_step_free()))
+            acc += static_cast<int64_t>((I.nx + width - 1) / width) * ((I.ny + rows - 1) / rows);
     }
     if (acc > INT32_MAX) return fail(BTRT_E_INVAL, "more than 2^31 - 1 tiles in one group");
     begin[n] = static_cast<int>(acc);
-    g.total[steps] = static_cast<int>(acc);
-    hipError_t e = hipMemcpyAsync(g.d_begin[steps], begin.data(), (n + 1) * sizeof(int), hipMemcpyHostToDevice,
+    P.total[slot] = static_cast<int>(acc);
+    hipError_t e = hipMemcpyAsync(P.d_begin[slot], begin.data(), (n + 1) * sizeof(int), hipMemcpyHostToDevice,
                                   g.stream);
     if (e == hipSuccess) e = hipStreamSynchronize(g.stream);
     return e == hipSuccess ? static_cast<int>(BTRT_OK) : hip_fail(e, "group table upload");
 }
 
-// The strip table of the k-step walker for the configured strip height (built when first
-// needed).
-int ensure_walk_table(Group& g, int k)
+// The unit tables of k steps per launch for the configured strip height (built when first needed).
+int ensure_table(Group& g, int k)
 {
-    const int rows = strip_rows(g.cfg);
-    if (g.walk_rows[k] == rows || g.inst.empty()) return BTRT_OK;
-    int rc = upload_begin(g, k, rows);
-    if (rc == BTRT_OK) g.walk_rows[k] = rows;
-    return rc;
+    for (int p = 0; p < 2; ++p) {
+        const int rows = unit_rows(g, p, k);
+        if (g.part[p].built_rows[k] == rows || g.part[p].inst.empty()) continue;
+        int rc = upload_begin(g, p, k, k, rows, false);
+        if (rc != BTRT_OK) return rc;
+        g.part[p].built_rows[k] = rows;
+    }
+    return BTRT_OK;
 }
 
 void advance(Group& g, int steps, int launches)
@@ -93,6 +121,8 @@ void advance(Group& g, int steps, int launches)
 
 int launch_once(Group& g, int steps)
 {
+    int rc = ensure_table(g, steps);
+    if (rc != BTRT_OK) return rc;
     hipError_t e = raw_launch(g, steps, g.flip);
     if (e != hipSuccess) return hip_fail(e, "batch sweep launch");
     advance(g, steps, 1);
@@ -120,16 +150,16 @@ int build_graph(Group& g)
 }
 
 template <typename T>
-void fill_entries(const Group& g, std::vector<BatchEntry<T>>& ent, bool nts)
+void fill_entries(const Group::Part& P, std::vector<BatchEntry<T>>& ent, bool nts)
 {
-    ent.resize(g.inst.size());
-    for (size_t i = 0; i < g.inst.size(); ++i) {
-        const Instance& I = *g.inst[i];
+    ent.resize(P.inst.size());
+    for (size_t i = 0; i < P.inst.size(); ++i) {
+        const Instance& I = *P.inst[i];
         for (int p = 0; p < 2; ++p) {
             ent[i].a[p] = sweep_args<T>(I, p);
             ent[i].a[p].nts = nts ? 1 : 0;
         }
-        ent[i].variant = 2 * I.kind + (I.k1_per_node ? 1 : 0);
+        ent[i].variant = 2 * (I.mom ? (I.kind != btrtk::kSrcNone ? 1 : 0) : I.kind) + (I.k1_per_node ? 1 : 0);
         ent[i].pad = 0;
     }
 }
@@ -153,21 +183,25 @@ int group_init(Group& g, int device, hipStream_t s, int precision, int capacity)
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, device) == hipSuccess && prop.multiProcessorCount > 0)
         g.ncu = prop.multiProcessorCount;
-    const size_t bytes = align_up(capacity * entry_bytes(precision)) +
-                         6 * align_up(static_cast<size_t>(capacity + 1) * sizeof(int));
+    // Per part: entries, unit offsets for 1, 2, 4, 6 and 7 steps and for a first step, parities.
+    const size_t ints = align_up(static_cast<size_t>(capacity + 1) * sizeof(int));
+    const size_t bytes = 2 * (align_up(capacity * entry_bytes(precision)) + 7 * ints);
     if (hipMalloc(reinterpret_cast<void**>(&g.tables), bytes) != hipSuccess) {
         g.tables = nullptr;
         (void)hipGetLastError();
         return fail(BTRT_E_NOMEM, "hipMalloc of %zu bytes failed", bytes);
     }
     char* t = g.tables;
-    g.d_ent = t;
-    t += align_up(capacity * entry_bytes(precision));
-    for (int k : {1, 2, 4, 6, 7}) {
-        g.d_begin[k] = reinterpret_cast<int*>(t);
-        t += align_up(static_cast<size_t>(capacity + 1) * sizeof(int));
+    for (Group::Part& P : g.part) {
+        P.d_ent = t;
+        t += align_up(capacity * entry_bytes(precision));
+        for (int k : {0, 1, 2, 4, 6, 7}) {
+            P.d_begin[k] = reinterpret_cast<int*>(t);
+            t += ints;
+        }
+        P.d_par = reinterpret_cast<int*>(t);
+        t += ints;
     }
-    g.d_par = reinterpret_cast<int*>(t);
     if (hipHostMalloc(reinterpret_cast<void**>(&g.h_res),
                       static_cast<size_t>(capacity) * kReducePartials * sizeof(double)) != hipSuccess) {
         g.h_res = nullptr;
@@ -182,51 +216,78 @@ int group_upload(Group& g)
     const int n = static_cast<int>(g.inst.size());
     if (n > g.capacity) return fail(BTRT_E_INVAL, "group of %d exceeds its capacity %d", n, g.capacity);
     g.flip = 0;
-    for (int k = 0; k <= btrtk::kBatchMaxSteps; ++k) {
-        g.walk_rows[k] = 0;
-        if (n == 0) g.total[k] = 0;
-    }
-    if (n == 0) return BTRT_OK;
-    std::vector<int> par(n);
-    hipError_t e = hipSuccess;
-    for (int steps = 1; steps <= 2; ++steps) {
-        int rc = upload_begin(g, steps, btrtk::tile_rows(steps, g.precision == BTRT_F64 ? 8 : 4));
-        if (rc != BTRT_OK) return rc;
-    }
-    for (int i = 0; i < n; ++i) par[i] = g.inst[i]->cur;
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(g.d_par, par.data(), n * sizeof(int), hipMemcpyHostToDevice, g.stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(g.stream);
     double state = 0;
-    for (const Instance* I : g.inst) state += 2.0 * 10.0 * I->plane * (g.precision == BTRT_F64 ? 8 : 4);
-    const bool nts = state > 256.0 * 1024 * 1024;  // the members' state exceeds the Infinity Cache
-    g.nts = nts;
-    if (e == hipSuccess) {
-        if (g.precision == BTRT_F64) {
+    for (const Instance* I : g.inst) state += 2.0 * (I->state_planes() + 1.0) * I->plane * (g.precision == BTRT_F64 ? 8 : 4);
+    g.nts = state > 256.0 * 1024 * 1024;  // the members' state exceeds the Infinity Cache
+    for (int p = 0; p < 2; ++p) {
+        Group::Part& P = g.part[p];
+        P.inst.clear();
+        for (Instance* I : g.inst)
+            if ((I->mom ? 1 : 0) == p) P.inst.push_back(I);
+        for (int k = 0; k <= btrtk::kBatchMaxSteps; ++k) P.built_rows[k] = P.total[k] = 0;
+        if (P.inst.empty()) continue;
+        std::vector<int> par(P.inst.size());
+        for (size_t i = 0; i < P.inst.size(); ++i) par[i] = P.inst[i]->cur;
+        hipError_t e = hipMemcpyAsync(P.d_par, par.data(), par.size() * sizeof(int), hipMemcpyHostToDevice, g.stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(g.stream);
+        if (e == hipSuccess && g.precision == BTRT_F64) {
             std::vector<BatchEntry<double>> ent;
-            fill_entries(g, ent, nts);
-            e = hipMemcpyAsync(g.d_ent, ent.data(), ent.size() * sizeof(ent[0]), hipMemcpyHostToDevice, g.stream);
+            fill_entries(P, ent, g.nts);
+            e = hipMemcpyAsync(P.d_ent, ent.data(), ent.size() * sizeof(ent[0]), hipMemcpyHostToDevice, g.stream);
             if (e == hipSuccess) e = hipStreamSynchronize(g.stream);
-        } else {
+        } else if (e == hipSuccess) {
             std::vector<BatchEntry<float>> ent;
-            fill_entries(g, ent, nts);
-            e = hipMemcpyAsync(g.d_ent, ent.data(), ent.size() * sizeof(ent[0]), hipMemcpyHostToDevice, g.stream);
+            fill_entries(P, ent, g.nts);
+            e = hipMemcpyAsync(P.d_ent, ent.data(), ent.size() * sizeof(ent[0]), hipMemcpyHostToDevice, g.stream);
             if (e == hipSuccess) e = hipStreamSynchronize(g.stream);
         }
+        if (e != hipSuccess) return hip_fail(e, "group table upload");
     }
-    return e == hipSuccess ? static_cast<int>(BTRT_OK) : hip_fail(e, "group table upload");
+    return BTRT_OK;
 }
+
+namespace {
+
+// The first step of members whose planes already hold it changes their count alone; where others
+// must take a step with them, those do so in a launch of their own.
+int first_step(Group& g)
+{
+    size_t free_members = 0;
+    for (const Instance* I : g.inst) free_members += I->first_step_free() ? 1 : 0;
+    if (free_members == 0) return 0;
+    if (free_members < g.inst.size()) {
+        for (int p = 0; p < 2; ++p) {
+            int rc = upload_begin(g, p, 0, 1, unit_rows(g, p, 1), true);
+            if (rc != BTRT_OK) return -rc;
+        }
+        for (int p = 0; p < 2; ++p) {
+            hipError_t e = part_launch(g, p, 0, 1, g.flip);
+            if (e != hipSuccess) return -hip_fail(e, "batch sweep launch");
+        }
+        advance(g, 1, 1);  // members passed over hold their state in both buffers
+    } else {
+        for (Instance* I : g.inst) I->step += 1;
+    }
+    return 1;
+}
+
+}  // namespace
 
 int group_enqueue(Group& g, int64_t n)
 {
     if (g.inst.empty()) return BTRT_OK;
-    if (btrtk::batch_walks(g.cfg.steps_per_launch)) {
-        int rc = ensure_walk_table(g, g.cfg.steps_per_launch);
-        if (rc != BTRT_OK) return rc;
+    int64_t left = n;
+    if (left > 0) {
+        const int done = first_step(g);
+        if (done < 0) return -done;
+        left -= done;
     }
     const int k = g.cfg.steps_per_launch;
     const int L = g.cfg.graph_launches;
-    int64_t left = n;
+    if (left >= k) {
+        int rc = ensure_table(g, k);
+        if (rc != BTRT_OK) return rc;
+    }
     if (L > 0) {
         const int64_t chunk = static_cast<int64_t>(L) * k;
         if (left >= chunk + (g.flip ? k : 0)) {
@@ -320,6 +381,7 @@ int group_tune(Group& g, int64_t max_steps, btrt_batch_config_t* best, int64_t* 
             g.cfg = cand[c];
             int r = group_enqueue(g, warm_k);
             used += warm_k;
+            if (r == BTRT_OK) r = ensure_table(g, k);
             if (r == BTRT_OK && cand[c].graph_launches > 0) r = build_graph(g);
             if (r != BTRT_OK) return r;
             (void)hipEventRecord(t0, g.stream);

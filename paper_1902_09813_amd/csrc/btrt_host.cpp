@@ -319,6 +319,9 @@ void fill_constants(Instance& I, SweepArgs<T>& a, const btrt_flux_t* B, const bt
     a.cq[1] = T(-4.5);
     a.cq[2] = T(-9);
     a.cq[3] = T(9);
+    a.m3[0] = T(3) * a.a11;
+    a.m3[1] = T(3) * a.a12;
+    a.m3[2] = T(3) * a.a22;
     a.src_amp = static_cast<T>(R && R->kind == BTRT_SRC_SIN ? R->amp : 0.0);
     a.src = I.kind == kSrcNone ? nullptr : reinterpret_cast<const T*>(I.mem + I.L.src);
     a.src_y = I.kind == kSrcSep ? reinterpret_cast<const T*>(I.mem + I.L.src_y) : nullptr;
@@ -329,7 +332,8 @@ void fill_constants(Instance& I, SweepArgs<T>& a, const btrt_flux_t* B, const bt
     a.fq = static_cast<T>(B->c[0] != 0.0 || B->c[1] != 0.0 ? B->q : 1.0);
     a.rr = static_cast<T>(R ? R->r : 0.0);
     a.rp = static_cast<T>(R && R->r != 0.0 ? R->p : 1.0);
-    a.dpoly = r.dq[0] != 0.0 ? 1 : 0;
+    a.dpoly = r.dq[0] != 0.0 && !I.mom ? 1 : 0;
+    a.mom_g = I.mom && (I.kind != kSrcNone || a.rr != T(0)) ? 1 : 0;
     a.dg = static_cast<T>(r.dq[1]);
     a.de = static_cast<T>(r.dq[2]);
     a.ds = static_cast<T>(r.dq[3]);
@@ -360,7 +364,12 @@ int instance_setup(Instance& I, const btrt_grid_t* grid, const btrt_flux_t* B, c
     I.k0_one = r.k0 == 1.0;
     I.afield = r.afield;
     I.growth = r.growth;
-    I.gen = r.gen;
+    I.gen = I.gen_problem = r.gen;
+    // The moment form: k0 = 1 and every second-order rate 1 leave nothing else of f+ (a term
+    // D = d(phi) I other than phi I would).
+    const bool phi_i = r.dq[0] == 0.0 || (r.dq[1] == 1.0 && r.dq[2] == 0.0);
+    I.mom = r.k0 == 1.0 && r.K2[0] == 1.0 && r.K2[3] == 1.0 && 0.5 * (r.K2[1] + r.K2[2]) == 1.0 && phi_i &&
+            (grid->precision == BTRT_F64 || grid->precision == BTRT_F32);
     I.wtab = nullptr;
     I.wall_t0 = 0;
     I.wall_limit = INT64_MAX;
@@ -447,7 +456,10 @@ int instance_setup(Instance& I, const btrt_grid_t* grid, const btrt_flux_t* B, c
     // The init kernel writes through a sweep's outputs: parity 1 outputs are f[0] and phi[0].
     const double ab[4] = {B->a[0], B->a[1], B->b[0], B->b[1]};
     const double cq[3] = {B->c[0], B->c[1], B->c[0] != 0.0 || B->c[1] != 0.0 ? B->q : 1.0};
-    if (I.precision == BTRT_F64)
+    if (I.mom)
+        err = I.precision == BTRT_F64 ? launch_mom_init<double>(sweep_args<double>(I, 1), I.kind, tmp, s)
+                                      : launch_mom_init<float>(sweep_args<float>(I, 1), I.kind, tmp, s);
+    else if (I.precision == BTRT_F64)
         err = launch_init<double>(sweep_args<double>(I, 1), kFmtPlain, tmp, I.wall, ab, cq, r.dq, s);
     else
         err = launch_init<float>(sweep_args<float>(I, 1), format_of(I.precision), tmp, I.wall, ab, cq, r.dq, s);
@@ -538,6 +550,8 @@ GatherArgs<T> gather_args(const Instance& I)
     g.out = reinterpret_cast<double*>(I.mem + I.L.tmp);
     g.partial = reinterpret_cast<double*>(I.mem + I.L.partial);
     g.population = -1;
+    g.mom = I.mom ? 1 : 0;
+    g.fresh = I.first_step_free() ? 1 : 0;
     return g;
 }
 
@@ -589,10 +603,16 @@ int instance_steps(Instance& I, const LaunchCfg& want, int64_t n, hipStream_t s)
     if (n > I.wall_limit - I.step)
         return fail(BTRT_E_INVAL, "%lld steps from step %lld go past the wall schedule (it ends at step %lld)",
                     static_cast<long long>(n), static_cast<long long>(I.step), static_cast<long long>(I.wall_limit));
+    if (I.first_step_free()) {
+        I.step = 1;
+        --n;
+    }
     const LaunchCfg c = instance_resolve(I, want);
+    const int per = c.fuse > 0 ? c.fuse : c.steps;
     for (int64_t i = 0; i < n;) {
         LaunchCfg k = c;
-        k.steps = static_cast<int>(std::min<int64_t>(c.steps, n - i));
+        k.steps = static_cast<int>(std::min<int64_t>(per, n - i));
+        if (I.mom && I.gen) k.steps = k.steps >= 4 ? 4 : (k.steps >= 2 ? 2 : 1);  // the launches it has
         if (k.steps != 2) k.tile = 0;
         if (k.steps == 1 && c.steps != 1) k.rows = k.group = 0;  // the one-step kernel's own tiles
         int rc = instance_launch(I, k, s);

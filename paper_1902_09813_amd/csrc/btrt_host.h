@@ -77,6 +77,8 @@ struct Instance {
     // corner means); the pull at step count t reads entry (t - wall_t0) at
     // wtab + (t - wall_t0) * wall_stride. Steps may advance the count up to wall_limit.
     bool gen = false;
+    bool gen_problem = false;  // the problem itself selects it (not a wall schedule)
+    bool mom = false;          // the state is in the moment form (k0 = 1, K2 = 1, plain storage; btrt_mom.h)
     const char* wtab = nullptr;
     int64_t wall_t0 = 0;
     int64_t wall_limit = INT64_MAX;
@@ -95,9 +97,15 @@ struct Instance {
     int kmode() const
     {
         const int k1 = afield ? btrtk::kK1Field : (k1_per_node ? btrtk::kK1Phi : btrtk::kK1Const);
+        if (mom) return k1 | btrtk::kMom | (gen ? btrtk::kGen : 0);
         if (gen) return k1 | btrtk::kGen;
         return k0_one ? (k1 | btrtk::kK0One) : k1;
     }
+    // Planes of a population buffer that hold the state.
+    int state_planes() const { return mom ? (mom_g() ? 3 : 2) : 9; }
+    bool mom_g() const { return precision == BTRT_F64 ? a64.mom_g != 0 : a32.mom_g != 0; }
+    // A moment-form state whose first step is already in its planes: it changes the count alone.
+    bool first_step_free() const { return mom && step == 0; }
     // Samples per step of a wall schedule: each side every half spacing, corners included.
     int wall_entry_values() const { return 4 * (nx + ny) + 4; }
     // Device slots per wall-table entry: the samples and the means at the four corners.
@@ -152,12 +160,18 @@ struct Group {
     int ncu = 256;
     int capacity = 0;
     std::vector<Instance*> inst;
-    char* tables = nullptr;  // device: entries, tile offsets (1- and 2-step tiles, walker strips), parities
-    void* d_ent = nullptr;
-    int* d_begin[btrtk::kBatchMaxSteps + 1] = {};  // indexed by steps per launch (1, 2, 4, 6, 7)
-    int* d_par = nullptr;
-    int total[btrtk::kBatchMaxSteps + 1] = {};
-    int walk_rows[btrtk::kBatchMaxSteps + 1] = {};  // strip height each walker table was built for (0: not built)
+    char* tables = nullptr;  // device: per part the entries, unit offsets and parities
+    // The members by the form of their state (part 0: populations, part 1: moments), each with its
+    // own kernels and so a launch of its own.
+    struct Part {
+        std::vector<Instance*> inst;
+        void* d_ent = nullptr;
+        int* d_begin[btrtk::kBatchMaxSteps + 1] = {};  // indexed by steps per launch (1, 2, 4, 6, 7); 0: see below
+        int* d_par = nullptr;
+        int total[btrtk::kBatchMaxSteps + 1] = {};
+        int built_rows[btrtk::kBatchMaxSteps + 1] = {};  // strip height each table was built for (0: not built)
+    };
+    Part part[2];
     int flip = 0;       // launches since group_upload, mod 2
     bool nts = false;   // the members' state exceeds the Infinity Cache: non-temporal stores in the
                         // one- and two-step batch kernels

@@ -31,6 +31,9 @@ constexpr int kK0One = 8;
 // kRcp1 (set by the 16-bit deviation formats' call sites, not a kernel variant): the FP32 1/det M
 // of the per-node K1 from the hardware reciprocal and one Newton step instead of a division.
 constexpr int kRcp1 = 16;
+// kMom: the moment form (btrt_mom.h), for k0 = 1 and K2 = 1 in plain FP64/FP32 storage: the planes of
+// a population buffer hold (qx, qy, g) instead of nine populations. With kGen for the general model.
+constexpr int kMom = 32;
 
 constexpr int kMaxFuse = 7;   // most time steps one sweep launch can fuse
 constexpr int kAutoFuse = 4;  // steps per launch of the automatic shape on large grids
@@ -55,6 +58,8 @@ struct SweepArgs {
     T cq[4];           // the collision's constants 3/2, -9/2, -9, 9 (read from the arguments, the
                        // kernels keep them in scalar registers instead of copying an accumulator
                        // for every multiply-add with an inline constant)
+    T m3[3];           // 3 (a11, a12, a22), read from the arguments by the moment form (uniform products
+                       // formed in a kernel hold vector registers)
     T src_amp;
     T sfac[kMaxFuse];  // source factor of each step of the launch (1: time independent)
     T fcx, fcy, fq;    // kGen: B(phi) gains (fcx, fcy) |phi|^fq
@@ -69,6 +74,8 @@ struct SweepArgs {
     T dev_scale, dev_inv; // 16-bit deviation formats: h = q(dev_scale (f+ - f_eq)), f+ = f_eq + h dev_inv
     int tiles_x, tiles_y; // set by the launcher for the kernel it picks
     int rows;             // rows per strip of the strip walkers (set by the launcher)
+    int edge_rows;        // moment walkers: rows of the first and last band on a grid with y walls (0: rows)
+    int mom_g;            // moment form: the state has a g plane (a source of any kind makes g differ from phi)
     int nts;              // 1: the one-step and two-step tile kernels store non-temporally (grids
                           // much larger than the caches; the launcher picks the kernel by it)
 };
@@ -87,6 +94,8 @@ struct GatherArgs {
     double* out;       // dense nx*ny output for field / population reads
     double* partial;   // per-block partial sums (kReducePartials doubles per block)
     int population;    // population index for the population read, -1 for phi
+    int mom;           // the planes hold the moment form
+    int fresh;         // moment form at step 0: phi(0) is in its plane (see btrt_mom.h)
 };
 
 // One instance of a batched launch: its arguments for both buffer parities and the kernel
@@ -108,6 +117,9 @@ struct LaunchCfg {
     int rows = 0;   // strip walkers (steps >= 2): rows per strip (0: automatic)
     int group = 0;  // strip walkers: strips per workgroup, 1 or kWalkGroup (0: automatic)
     int tile = 0;   // 1: steps == 2 through the LDS tile kernel instead of a strip walker
+    // Set by resolve_launch for automatic shapes of the moment form; not part of the public shape.
+    int fuse = 0;       // time steps the launches take where they differ from `steps` (0: steps)
+    int fit_rows = 0;   // rows per strip fitted to the resident wavefront slots (0: rows)
 };
 constexpr int kWalkGroup = 4;
 
@@ -145,6 +157,15 @@ template <typename T>
 hipError_t launch_batch_sweep(const BatchEntry<T>* ent, const int* begin, const int* par, int ninst, int total_tiles,
                               int flip, int steps, int grid, int rows, bool k0one, bool nts, hipStream_t s);
 int batch_strip_columns(int steps);
+// The same for instances in the moment form, whose units are 64 x tile_rows tiles for one step and
+// strips of mom_strip_columns(steps) columns otherwise (rows high).
+template <typename T>
+hipError_t launch_batch_mom(const BatchEntry<T>* ent, const int* begin, const int* par, int ninst, int total, int flip,
+                            int steps, int grid, int rows, hipStream_t s);
+int mom_strip_columns(int steps);
+// f+(0) of the moment form into both buffers of a handle (a: the arguments of parity 1).
+template <typename T>
+hipError_t launch_mom_init(const SweepArgs<T>& a, int kind, const double* phi0, hipStream_t s);
 // Tile height of the kernel that fuses `steps` steps (tile width is 64).
 int tile_rows(int steps, int precision_bytes);
 constexpr int kTileWidth = 64;

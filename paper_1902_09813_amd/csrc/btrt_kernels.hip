@@ -2,7 +2,7 @@
 // dispatch of the sweep launchers (the sweeps themselves live in btrt_sweep_<format>.hip and
 // the batched launchers in btrt_batch_kernels.hip; the device code in btrt_device.h).
 
-#include "btrt_device.h"
+#include "btrt_mom.h"
 
 namespace btrtk {
 namespace {
@@ -55,26 +55,86 @@ __device__ __forceinline__ void pull_any(const SweepArgs<typename F::T>& a, int 
         F::template pull<false>(a, x, y, f);
 }
 
+// f+(0) of the moment form, pointwise from phi0 (q = B(phi0), g = phi0 + S(0)), into both buffers, so
+// that a launch of a batch may pass over an instance without a step of its own.
+template <typename T>
+__global__ __launch_bounds__(kBlock) void mom_init_kernel(SweepArgs<T> a, int kind, const double* __restrict__ phi0)
+{
+    const int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
+    if (k >= static_cast<int64_t>(a.nx) * a.ny) return;
+    const int y = static_cast<int>(k / a.nx);
+    const int x = static_cast<int>(k - static_cast<int64_t>(y) * a.nx);
+    const int n = y * a.pitch + x;
+    const T phi = static_cast<T>(phi0[k]);
+    T Bx = phi * fmadd(T(0.5) * a.bx, phi, a.ax), By = phi * fmadd(T(0.5) * a.by, phi, a.ay);
+    if (a.fcx != T(0) || a.fcy != T(0)) {
+        const T pw = abspow(phi, a.fq);
+        Bx = fmadd(a.fcx, pw, Bx);
+        By = fmadd(a.fcy, pw, By);
+    }
+    T* const in = const_cast<T*>(a.fin);
+    T* const phi_in = const_cast<T*>(a.phi_prev);
+    a.phi_out[n] = phi_in[n] = phi;
+    a.fout[kMomQx * a.plane + n] = in[kMomQx * a.plane + n] = Bx;
+    a.fout[kMomQy * a.plane + n] = in[kMomQy * a.plane + n] = By;
+    if (a.mom_g) {
+        T s = kind != kSrcNone ? mom_source(a, n, x, y) : T(0);
+        if (a.rr != T(0)) s = s + (a.rr * phi) * (T(1) - abspow(phi, a.rp));
+        a.fout[kMomG * a.plane + n] = in[kMomG * a.plane + n] = phi + s;
+    }
+}
+
+// phi(t) at node (x, y).
+template <typename F>
+__device__ __forceinline__ typename F::T phi_at(const GatherArgs<typename F::T>& a, int x, int y)
+{
+    using T = typename F::T;
+    if constexpr (plain_format<F>()) {
+        if (a.mom) {
+            if (a.fresh) return a.s.phi_prev[y * a.s.pitch + x];
+            return a.s.wtab != nullptr ? mom_pull<T, true>(a.s, x, y).phi : mom_pull<T, false>(a.s, x, y).phi;
+        }
+    }
+    T f[9];
+    pull_any<F>(a.s, x, y, f);
+    return sum9(f);
+}
+
+// f_i(t) at node (x, y) (moment form: what the pull stands for; f^eq(phi0) at step 0).
+template <typename F>
+__device__ __forceinline__ typename F::T population_at(const GatherArgs<typename F::T>& a, int x, int y, int i)
+{
+    using T = typename F::T;
+    if constexpr (plain_format<F>()) {
+        if (a.mom) {
+            if (a.fresh) {
+                const int n = y * a.s.pitch + x;
+                const T* q = a.s.fin;
+                const T w = i == 0 ? Lat<T>::w0 : (i < 5 ? Lat<T>::w1 : Lat<T>::w5);
+                return w * fmadd(T(3), T(dir_cx(i)) * q[kMomQx * a.s.plane + n] + T(dir_cy(i)) * q[kMomQy * a.s.plane + n],
+                                 a.s.phi_prev[n]);
+            }
+            return a.s.wtab != nullptr ? mom_population<T, true>(a.s, x, y, i) : mom_population<T, false>(a.s, x, y, i);
+        }
+    }
+    T f[9];
+    pull_any<F>(a.s, x, y, f);
+    T v = T(0);
+#pragma unroll
+    for (int j = 0; j < 9; ++j)
+        if (j == i) v = f[j];
+    return v;
+}
+
 // phi(t) (or one population f_i(t)) at every node into a dense FP64 array.
 template <typename F>
 __global__ __launch_bounds__(kBlock) void gather_field_kernel(GatherArgs<typename F::T> a)
 {
-    using T = typename F::T;
     const int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
     if (k >= static_cast<int64_t>(a.s.nx) * a.s.ny) return;
     const int y = static_cast<int>(k / a.s.nx);
     const int x = static_cast<int>(k - static_cast<int64_t>(y) * a.s.nx);
-    T f[9];
-    pull_any<F>(a.s, x, y, f);
-    T v = T(0);
-    if (a.population < 0) {
-        v = sum9(f);
-    } else {
-#pragma unroll
-        for (int i = 0; i < 9; ++i)
-            if (i == a.population) v = f[i];
-    }
-    a.out[k] = static_cast<double>(v);
+    a.out[k] = static_cast<double>(a.population < 0 ? phi_at<F>(a, x, y) : population_at<F>(a, x, y, a.population));
 }
 
 __device__ __forceinline__ double wave_sum(double v)
@@ -115,16 +175,13 @@ __device__ __forceinline__ void block_reduce(double v[kReducePartials])
 template <typename F, int MODE>
 __global__ __launch_bounds__(kBlock) void reduce_kernel(GatherArgs<typename F::T> a)
 {
-    using T = typename F::T;
     double v[kReducePartials] = {0, 0, 0, 0, 0, 0};
     const int64_t nn = static_cast<int64_t>(a.s.nx) * a.s.ny;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * kBlock;
     for (int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; k < nn; k += stride) {
         const int y = static_cast<int>(k / a.s.nx);
         const int x = static_cast<int>(k - static_cast<int64_t>(y) * a.s.nx);
-        T f[9];
-        pull_any<F>(a.s, x, y, f);
-        const double phi = static_cast<double>(sum9(f));
+        const double phi = static_cast<double>(phi_at<F>(a, x, y));
         if (!isfinite(phi)) v[5] += 1.0;
         if constexpr (MODE == kResidual) {
             v[0] += fabs(phi - a.snap[k]);
@@ -216,6 +273,14 @@ template <typename T>
 hipError_t launch_sweep(const SweepArgs<T>& a, int fmt, int src_kind, int kmode, const LaunchCfg& cfg,
                         hipStream_t s)
 {
+    if ((kmode & kMom) != 0) {  // the moment form: plain storage only
+        if (fmt != kFmtPlain) return hipErrorInvalidValue;
+        const bool gen = (kmode & kGen) != 0;
+        if constexpr (sizeof(T) == 8)
+            return gen ? mom_gen_f64(a, src_kind, kmode, cfg, s) : mom_f64(a, src_kind, kmode, cfg, s);
+        else
+            return gen ? mom_gen_f32(a, src_kind, kmode, cfg, s) : mom_f32(a, src_kind, kmode, cfg, s);
+    }
     if ((kmode & kGen) != 0) {  // the general node model: plain storage only
         if (fmt != kFmtPlain) return hipErrorInvalidValue;
         if constexpr (sizeof(T) == 8)
@@ -247,6 +312,13 @@ hipError_t launch_sweep(const SweepArgs<T>& a, int fmt, int src_kind, int kmode,
 template <typename T>
 LaunchCfg resolve_launch(const SweepArgs<T>& a, int fmt, int src_kind, int kmode, LaunchCfg cfg)
 {
+    if ((kmode & kMom) != 0) {
+        const bool gen = (kmode & kGen) != 0;
+        if constexpr (sizeof(T) == 8)
+            return gen ? mom_resolve_gen_f64(a, src_kind, kmode, cfg) : mom_resolve_f64(a, src_kind, kmode, cfg);
+        else
+            return gen ? mom_resolve_gen_f32(a, src_kind, kmode, cfg) : mom_resolve_f32(a, src_kind, kmode, cfg);
+    }
     if ((kmode & kGen) != 0) {
         if constexpr (sizeof(T) == 8)
             return resolve_gen_f64(a, src_kind, kmode & ~kK0One, cfg);
@@ -280,6 +352,14 @@ hipError_t launch_init(const SweepArgs<T>& a, int fmt, const double* phi0, const
 }
 
 template <typename T>
+hipError_t launch_mom_init(const SweepArgs<T>& a, int kind, const double* phi0, hipStream_t s)
+{
+    const int64_t nn = static_cast<int64_t>(a.nx) * a.ny;
+    hipLaunchKernelGGL((mom_init_kernel<T>), dim3(blocks_for(nn)), dim3(kBlock), 0, s, a, kind, phi0);
+    return hipGetLastError();
+}
+
+template <typename T>
 hipError_t launch_gather_field(const GatherArgs<T>& a, int fmt, hipStream_t s)
 {
     BTRT_BY_FORMAT(T, gather_with_fmt, a, s);
@@ -306,6 +386,7 @@ hipError_t launch_convert(const double* in, T* out, int nx, int ny, int pitch, h
     template LaunchCfg resolve_launch<T>(const SweepArgs<T>&, int, int, int, LaunchCfg);                         \
     template hipError_t launch_init<T>(const SweepArgs<T>&, int, const double*, const double[4], const double[4],  \
                                        const double[3], const double[4], hipStream_t);                             \
+    template hipError_t launch_mom_init<T>(const SweepArgs<T>&, int, const double*, hipStream_t);                 \
     template hipError_t launch_gather_field<T>(const GatherArgs<T>&, int, hipStream_t);                           \
     template hipError_t launch_reduce<T>(const GatherArgs<T>&, int, int, double*, hipStream_t);                   \
     template hipError_t launch_convert<T>(const double*, T*, int, int, int, hipStream_t);                         \

@@ -1,0 +1,107 @@
+"""The moment form of the D2Q9 sweep (k0 = 1, K2 = 1 in FP64 and FP32 storage): its walkers, one-step
+kernel, reads and batched kernels at the sizes where they can go wrong.
+
+* FP64 against the oracle (1e-12 normwise, phi and every population) and every steps-per-launch count
+  against one step per launch bit for bit, around the strip widths (64 - 2k columns; 128 - 2k in
+  FP32 from six steps on) and for grids narrower than a strip, on every kind of boundary, with and
+  without sources, with constant, phi-dependent and space-dependent A.
+* The general model's kernels (power-law flux, reaction, wall schedule) with these rates.
+* A batch that mixes both forms of state, and a server whose requests join at different rounds: the
+  bits of single solves.
+"""
+import dataclasses
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1902_09813_amd import btrt
+from paper_1902_09813_amd import workloads as W
+from tests._cases import normwise, run_oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def say(msg):
+    print(msg, flush=True)
+    sys.stdout.flush()
+
+
+BCS = {"periodic": (0, 0, 0, 0), "walls": (1, 1, 1, 1), "y_walls": (0, 0, 1, 1), "x_walls": (1, 1, 0, 0)}
+SIZES = [(1, 1), (1, 7), (5, 2), (50, 33), (57, 16), (64, 64), (113, 15), (116, 9), (131, 70)]
+
+
+def case(nx, ny, bc, source=None, beta=0.0, **kw):
+    return W.Workload(f"mom_{nx}x{ny}", nx, ny, 0, flux_a=(0.03, -0.02), flux_b=(0.04, 0.01), A0=(0.02, 0.006, 0.012),
+                      beta=beta, source=source, bc_type=bc, bc_value=tuple(0.2 * (q + 1) * t for q, t in enumerate(bc)),
+                      seed=11, phi0_kind="uniform", **kw)
+
+
+def variants(nx, ny, bc):
+    rng = np.random.default_rng(nx + 7 * ny)
+    yield case(nx, ny, bc)
+    yield case(nx, ny, bc, source=("sin", 0.003, 1, 2), beta=0.7)
+    field = np.zeros((ny, nx, 3))
+    field[..., 0], field[..., 2] = rng.uniform(0.01, 0.05, (2, ny, nx))
+    yield case(nx, ny, bc, source=("field", 1e-3 * rng.standard_normal((ny, nx)), -1e-3), beta=0.3, A0_field=field)
+
+
+@pytest.mark.parametrize("bc", list(BCS), ids=list(BCS))
+@pytest.mark.parametrize("size", SIZES, ids=lambda s: f"{s[0]}x{s[1]}")
+def test_every_walk_against_one_step_and_the_oracle(size, bc):
+    steps = 15
+    for j, w in enumerate(variants(*size, BCS[bc])):
+        say(f"[gpu] moments {w.nx}x{w.ny} {bc} variant {j}")
+        o = run_oracle(w, steps)
+        for precision in (btrt.F64, btrt.F32):
+            want = None
+            for k in (1, 0, 2, 3, 4, 5, 6, 7):
+                with btrt.Solver(btrt.problem_from_workload(w, precision=precision), w.phi0()) as s:
+                    s.set_launch(k, 0, 0, 0).step(steps)
+                    got = (s.populations(), s.field())
+                if want is None:
+                    want = got
+                    if precision == btrt.F64:
+                        assert normwise(got[0], o.f) <= 1e-12 and normwise(got[1], o.phi()) <= 1e-12
+                assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), (k, precision)
+
+
+def test_general_model_with_unit_rates():
+    w = dataclasses.replace(W.bfe(n=17, t_end=0.4), k2=1.0)
+    say(f"[gpu] moments, general model {w.nx}x{w.ny} steps {w.steps}")
+    o = run_oracle(w)
+    want = None
+    for k in (1, 0, 2, 3, 4, 7):
+        with btrt.Solver(btrt.problem_from_workload(w), w.phi0()) as s:
+            s.set_walls(btrt.wall_schedule(w, 0, w.steps)).set_launch(k, 0, 0, 0).step(w.steps)
+            got = s.populations()
+            want = got if want is None else want
+            assert normwise(got, o.f) <= 1e-12 and np.array_equal(got, want), k
+
+
+def test_mixed_batch_and_late_requests():
+    mixed = [case(70, 33, BCS["walls"], beta=0.5), dataclasses.replace(case(41, 50, BCS["periodic"]), k0=0.9),
+             case(33, 64, BCS["y_walls"], source=("sin", 0.003, 1, 1)), dataclasses.replace(case(45, 45, BCS["walls"]), k2=1.2)]
+    steps = 29
+    for precision in (btrt.F64, btrt.F32):
+        alone = []
+        for w in mixed:
+            with btrt.Solver(btrt.problem_from_workload(w, precision=precision), w.phi0()) as s:
+                alone.append(s.set_fusion(1).step(steps).field())
+        for cfg in [(1, 0, 0, 0), (2, 0, 0, 0), (4, 0, 4, 16), (6, 1, 0, 8), (7, 0, 2, 0)]:
+            say(f"[gpu] mixed batch {cfg}")
+            with btrt.Batch([(btrt.problem_from_workload(w, precision=precision), w.phi0()) for w in mixed]) as b:
+                b.set_config(*cfg).step(steps)
+                for i in range(b.n):
+                    assert np.array_equal(b.field(i), alone[i]), (cfg, i)
+    # The second pair joins after the first pair's first round: steps 10 and 20 in one launch.
+    for launch in [(0, 0, 0, 0), (1, 0, 0, 0), (4, 0, 0, 8)]:
+        with btrt.Server(precision=btrt.F64, memory_bytes=1 << 27, check_interval=10, launch=launch) as srv:
+            ids = [srv.submit(btrt.problem_from_workload(w), w.phi0(), 0.0, 30) for w in mixed[:2]]
+            srv.pump()
+            ids += [srv.submit(btrt.problem_from_workload(w), w.phi0(), 0.0, 30) for w in mixed[2:]]
+            while any(srv.info(i)["status"] < btrt.REQ_DONE for i in ids):
+                srv.pump()
+            for i, w in zip(ids, mixed):
+                with btrt.Solver(btrt.problem_from_workload(w), w.phi0()) as s:
+                    assert np.array_equal(srv.result(i), s.set_fusion(1).step(30).field()), (launch, w.name)
