@@ -174,10 +174,12 @@ struct btrt3 {
     int precision = BTRT_F64;
     int nx = 0, ny = 0, nz = 0, pitch = 0;
     bool src = false, k1_per_node = false;
+    bool mom = false;  // the state is in the moment form (k0 = 1, K2 = 1; btrt3_mom.h)
     int cur = 0;
     int64_t step = 0;
     int check_interval = 1000;
     int cus = 256;                          // compute units of the device
+    int mom_chunks[3] = {0, 0, 0};          // mom_chunk by steps per launch, once computed
     btrt3_launch_t launch{0, 0, 0};         // as set (0: automatic)
     Sweep3<double> a64{};
     Sweep3<float> a32{};
@@ -218,6 +220,7 @@ void fill3(btrt3* h, Sweep3<T>& a, const btrt3_flux_t* B, const btrt3_diff_t* K,
     }
     for (int s = 0; s < 6; ++s) a.wall[s] = static_cast<T>(bc->type[s] == BTRT_DIRICHLET ? bc->value[s] : 0.0);
     for (int c = 0; c < 6; ++c) a.A0[c] = static_cast<T>(K->a0[c]);
+    for (int c = 0; c < 6; ++c) a.m3[c] = T(3) * a.A0[c];
     a.beta = static_cast<T>(K->beta);
     const double k1s[6] = {r.K1[0], r.K1[1], r.K1[2], r.K1[4], r.K1[5], r.K1[8]};
     for (int c = 0; c < 6; ++c) a.K1[c] = static_cast<T>(k1s[c]);
@@ -243,6 +246,8 @@ Gather3<T> gather_args(const btrt3* h)
     g.out = reinterpret_cast<double*>(h->mem + h->L.tmp);
     g.partial = reinterpret_cast<double*>(h->mem + h->L.partial);
     g.population = -1;
+    g.mom = h->mom ? 1 : 0;
+    g.fresh = h->mom && h->step == 0 ? 1 : 0;
     return g;
 }
 
@@ -280,12 +285,27 @@ int setup(btrt3* h, const btrt3_flux_t* B, const btrt3_diff_t* K, const btrt3_so
     e = hipMemcpyAsync(tmp, phi0, nn * sizeof(double), hipMemcpyHostToDevice, h->stream);
     if (e != hipSuccess) return hip_fail(e, "phi0 upload");
     // The init writes through the outputs of parity 1: f[0] and phi[0].
-    e = h->precision == BTRT_F64 ? launch3_init<double>(args<double>(h, 1), tmp, h->stream)
-                                 : launch3_init<float>(args<float>(h, 1), tmp, h->stream);
+    if (h->mom)
+        e = h->precision == BTRT_F64 ? launch3_mom_init<double>(args<double>(h, 1), tmp, h->stream)
+                                     : launch3_mom_init<float>(args<float>(h, 1), tmp, h->stream);
+    else
+        e = h->precision == BTRT_F64 ? launch3_init<double>(args<double>(h, 1), tmp, h->stream)
+                                     : launch3_init<float>(args<float>(h, 1), tmp, h->stream);
     if (e != hipSuccess) return hip_fail(e, "init launch");
     e = hipMemcpyAsync(h->mem + h->L.snap, tmp, nn * sizeof(double), hipMemcpyDeviceToDevice, h->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     return e == hipSuccess ? static_cast<int>(BTRT_OK) : hip_fail(e, "init");
+}
+
+// Steps per launch of the moment form with the automatic shape: two on periodic boxes from 2^20 nodes
+// up, else one (us a step with one and two: 74 x 58 x 46 FP64 8.9 and 9.8, FP32 6.4 and 7.9; 128 x 128
+// x 100 31.1 and 27.7, 19.7 and 18.0; 230 x 110 x 200 88.5 and 65.4; with Dirichlet faces, whose
+// bounce-back costs two steps more registers than there are, 118 and 380, 53.9 and 54.8).
+int mom_auto_steps(const btrt3* h)
+{
+    const int* per = h->precision == BTRT_F64 ? h->a64.per : h->a32.per;
+    const bool periodic = per[0] && per[1] && per[2];
+    return periodic && static_cast<int64_t>(h->nx) * h->ny * h->nz >= (int64_t(1) << 20) ? 2 : 1;
 }
 
 // Launch shape with the automatic fields resolved for the handle's grid.
@@ -320,6 +340,54 @@ btrt3_launch_t resolve_launch(const btrt3* h)
         }
     }
     return c;
+}
+
+// Planes per workgroup of a moment-form launch of `steps` steps: a workgroup walks its chunk plus
+// `steps` planes on each side, and the launch takes as many rounds of resident workgroups as it needs.
+int mom_chunk(btrt3* h, int steps)
+{
+    if (h->mom_chunks[steps] > 0) return h->mom_chunks[steps];
+    const int per_cu = h->precision == BTRT_F64 ? mom3_blocks_per_cu<double>(h->a64, h->k1_per_node, steps)
+                                                : mom3_blocks_per_cu<float>(h->a32, h->k1_per_node, steps);
+    const int64_t slots = static_cast<int64_t>(h->cus) * per_cu;
+    int64_t best = -1;
+    int chunk = h->nz;
+    for (int zc = 1; zc <= 256; ++zc) {
+        const int use = std::min(zc, h->nz);
+        const int64_t cost = ((mom3_workgroups(h->nx, h->ny, h->nz, steps, use) + slots - 1) / slots) * (use + 2 * steps);
+        if (best < 0 || cost < best) {
+            best = cost;
+            chunk = use;
+        }
+        if (use == h->nz) break;
+    }
+    h->mom_chunks[steps] = chunk;
+    return chunk;
+}
+
+// n steps of a handle in the moment form.
+int mom_steps(btrt3* h, const btrt3_launch_t& c, int64_t n)
+{
+    if (n > 0 && h->step == 0) {  // the planes already hold f+(0)
+        h->step = 1;
+        --n;
+    }
+    if (n <= 0) return BTRT_OK;
+    const int zc = h->launch.z_chunk;
+    int most = c.steps_per_launch;
+    if (h->launch.steps_per_launch == 0) most = mom_auto_steps(h);
+    while (n > 0) {
+        const int k = static_cast<int>(std::min<int64_t>(most, n));
+        const int chunk = zc > 0 && c.steps_per_launch == 2 ? zc : mom_chunk(h, k);
+        const hipError_t e = h->precision == BTRT_F64
+                                 ? launch3_mom<double>(args<double>(h, h->cur), h->k1_per_node, k, chunk, h->stream)
+                                 : launch3_mom<float>(args<float>(h, h->cur), h->k1_per_node, k, chunk, h->stream);
+        if (e != hipSuccess) return hip_fail(e, "sweep launch");
+        h->cur ^= 1;
+        h->step += k;
+        n -= k;
+    }
+    return BTRT_OK;
 }
 
 int reduce_sync(btrt3* h, int mode, double out[kPartials])
@@ -391,6 +459,9 @@ int btrt3_create(const btrt3_grid_t* grid, const btrt3_flux_t* B, const btrt3_di
     h->pitch = pitch_for(grid->nx, grid->precision);
     h->src = R && R->kind == BTRT_SRC_FIELD;
     h->k1_per_node = r.k1_per_node;
+    // The moment form: k0 = 1 and every second-order rate 1 leave nothing else of f+.
+    h->mom = r.k0 == 1.0 && r.K2[0] == 1.0 && r.K2[4] == 1.0 && r.K2[8] == 1.0 && 0.5 * (r.K2[1] + r.K2[3]) == 1.0 &&
+             0.5 * (r.K2[2] + r.K2[6]) == 1.0 && 0.5 * (r.K2[5] + r.K2[7]) == 1.0;
     h->check_interval = relax->check_interval;
     h->L = layout3(h->nx, h->ny, h->nz, h->precision, h->src);
     fill_info3(grid, r, h->src, &h->info);
@@ -434,6 +505,10 @@ int btrt3_step(btrt3_t* h, int64_t n)
     DeviceGuard g(h->device);
     if (g.status() != hipSuccess) return hip_fail(g.status(), "hipSetDevice");
     const btrt3_launch_t c = resolve_launch(h);
+    if (h->mom) {
+        const int rc = mom_steps(h, c, n);
+        return rc == BTRT_OK ? ok() : rc;
+    }
     for (int64_t s = 0; s < n;) {
         const bool two = c.steps_per_launch == 2 && n - s >= 2;
         const bool f64 = h->precision == BTRT_F64;

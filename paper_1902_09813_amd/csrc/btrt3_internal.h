@@ -31,6 +31,7 @@ struct Sweep3 {
     T cq[6];            // the collision's constants 3/2, -9/2, 3, -3, 9, -9 (from the arguments the
                         // kernels keep them in scalar registers, so a multiply-add needs no copy of
                         // its accumulator)
+    T m3[6];            // 3 A0, read from the arguments by the moment form
     T q2[6];            // K2 rates (k2_11, k2_12s, k2_13s, k2_22, k2_23s, k2_33), off-diagonals
                         // symmetrised (Eq. (100))
     int tiles_x, tiles_y;
@@ -47,6 +48,7 @@ struct Gather3 {
     double* out;        // dense output of field and population reads
     double* partial;    // per-block partial sums
     int population;     // -1: phi
+    int mom, fresh;     // the planes hold the moment form (btrt3_mom.h); at step 0 (phi(0) in its plane)
 };
 
 constexpr int kPartials = 6;
@@ -66,6 +68,15 @@ int64_t sweep2_workgroups(int nx, int ny, int nz, int tile, int zc);
 // for the variant a launch with these arguments takes; 1 if the runtime cannot tell.
 template <typename T>
 int sweep2_blocks_per_cu(bool walls, bool src, bool k1_per_node, int tile);
+// The moment form (btrt3_mom.h): `steps` (1 or 2) time steps in one launch over chunks of zc planes;
+// workgroups of a launch and how many of them a compute unit holds; f+(0) from phi0.
+template <typename T>
+hipError_t launch3_mom(const Sweep3<T>& a, bool k1_per_node, int steps, int zc, hipStream_t s);
+template <typename T>
+int mom3_blocks_per_cu(const Sweep3<T>& a, bool k1_per_node, int steps);
+int64_t mom3_workgroups(int nx, int ny, int nz, int steps, int zc);
+template <typename T>
+hipError_t launch3_mom_init(const Sweep3<T>& a, const double* phi0, hipStream_t s);
 // f+(-1) and phi(-1) := phi0 (FP64 values converted to T) into a.fout / a.phi_out.
 template <typename T>
 hipError_t launch3_init(const Sweep3<T>& a, const double* phi0, hipStream_t s);

@@ -17,7 +17,7 @@
 // the arithmetic is ~200 flops against 320 B (FP64), so the sweep is bandwidth-bound and there is
 // no matrix-core work.
 
-#include "btrt3_internal.h"
+#include "btrt3_mom.h"
 
 #include <algorithm>
 
@@ -572,6 +572,48 @@ __device__ __forceinline__ void dense_node(const Sweep3<T>& a, int64_t k, int& x
     z = static_cast<int>(k / (static_cast<int64_t>(a.nx) * a.ny));
 }
 
+// phi(t) at node (x, y, z), n its index.
+template <typename T>
+__device__ __forceinline__ T phi3_at(const Gather3<T>& g, int x, int y, int z)
+{
+    const Sweep3<T>& a = g.s;
+    if (g.mom) return g.fresh ? a.phi_prev[z * a.slab + y * a.pitch + x] : mom3_pull(a, x, y, z).phi;
+    T f[kQ];
+    pull3(a, x, y, z, f);
+    T s = T(0);
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) s += f[i];
+    return s;
+}
+
+// f_i(t) of the moment form: what the pull stands for; f^eq(phi0) at step 0.
+template <typename T>
+__device__ __forceinline__ T mom3_population(const Gather3<T>& g, int x, int y, int z, int i)
+{
+    const Sweep3<T>& a = g.s;
+    auto post = [&](int n, const T* gp, T sign) {
+        const T cq = T(cxv(i)) * a.fin[kM3Qx * a.plane + n] + T(cyv(i)) * a.fin[kM3Qy * a.plane + n] +
+                     T(czv(i)) * a.fin[kM3Qz * a.plane + n];
+        return wv<T>(i) * fmadd(sign * T(3), cq, gp[n]);
+    };
+    const int n = z * a.slab + y * a.pitch + x;
+    if (g.fresh) return post(n, a.phi_prev, T(1));
+    const T* gp = a.src ? a.fin + kM3G * a.plane : a.phi_prev;
+    int s[3] = {x - cxv(i), y - cyv(i), z - czv(i)};
+    const int dim[3] = {a.nx, a.ny, a.nz};
+    int faces = 0;
+    T wsum = T(0);
+    for (int c = 0; c < 3; ++c) {
+        if (s[c] < 0) {
+            if (a.per[c]) s[c] += dim[c]; else { ++faces; wsum += a.wall[2 * c]; }
+        } else if (s[c] >= dim[c]) {
+            if (a.per[c]) s[c] -= dim[c]; else { ++faces; wsum += a.wall[2 * c + 1]; }
+        }
+    }
+    if (faces == 0) return post(s[2] * a.slab + s[1] * a.pitch + s[0], gp, T(1));
+    return fmadd(T(2) * wv<T>(i), faces == 1 ? wsum : T(0.5) * wsum, -post(n, gp, T(-1)));
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void gather3_kernel(Gather3<T> g)
 {
@@ -580,13 +622,14 @@ __global__ __launch_bounds__(kBlock) void gather3_kernel(Gather3<T> g)
     if (k >= static_cast<int64_t>(a.nx) * a.ny * a.nz) return;
     int x, y, z;
     dense_node(a, k, x, y, z);
-    T f[kQ];
-    pull3(a, x, y, z, f);
     T v = T(0);
     if (g.population < 0) {
-#pragma unroll
-        for (int i = 0; i < kQ; ++i) v += f[i];
+        v = phi3_at(g, x, y, z);
+    } else if (g.mom) {
+        v = mom3_population(g, x, y, z, g.population);
     } else {
+        T f[kQ];
+        pull3(a, x, y, z, f);
 #pragma unroll
         for (int i = 0; i < kQ; ++i)
             if (i == g.population) v = f[i];
@@ -637,12 +680,7 @@ __global__ __launch_bounds__(kBlock) void reduce3_kernel(Gather3<T> g)
     for (int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x; k < nn; k += stride) {
         int x, y, z;
         dense_node(a, k, x, y, z);
-        T f[kQ];
-        pull3(a, x, y, z, f);
-        T s = T(0);
-#pragma unroll
-        for (int i = 0; i < kQ; ++i) s += f[i];
-        const double phi = static_cast<double>(s);
+        const double phi = static_cast<double>(phi3_at(g, x, y, z));
         if (!isfinite(phi)) v[5] += 1.0;
         if constexpr (MODE == 0) {
             v[0] += fabs(phi - g.snap[k]);

@@ -1,0 +1,50 @@
+"""The moment form of the D3Q19 sweep (k0 = 1, K2 = 1): against the oracle (FP64, 1e-12 normwise) and
+bit for bit between one and two steps per launch and chunk heights, around the tile sizes (62 x 6
+output columns with one step per launch, 60 x 12 with two), for boxes thinner than a tile, on every
+kind of boundary (edges and corners of the box with unequal face values), with and without a source.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1902_09813_amd import btrt, btrt3
+from paper_1902_09813_amd import workloads as W
+from tests._cases import normwise, run_oracle3
+
+pytestmark = pytest.mark.gpu
+
+BCS = [(0, 0, 0, 0, 0, 0), (1, 1, 1, 1, 1, 1), (1, 1, 0, 0, 0, 0), (0, 0, 1, 1, 0, 0), (0, 0, 0, 0, 1, 1)]
+SIZES = [(1, 1, 1), (2, 7, 3), (60, 12, 4), (61, 13, 5), (63, 6, 2), (124, 5, 9)]
+
+
+def box(nx, ny, nz, bc, source, beta):
+    rng = np.random.default_rng(nx + 3 * ny + 5 * nz)
+    return W.Workload3(f"mom3_{nx}x{ny}x{nz}", nx, ny, nz, 9, flux_a=(0.02, -0.01, 0.015), flux_b=(0.03, 0.01, -0.02),
+                       A0=(0.05, 0.01, 0.005, 0.04, -0.008, 0.03), beta=beta,
+                       source=1e-3 * rng.standard_normal((nz, ny, nx)) if source else None, bc_type=bc,
+                       bc_value=tuple(0.15 * (f + 1) * t for f, t in enumerate(bc)), phi0_array=rng.random((nz, ny, nx)))
+
+
+@pytest.mark.parametrize("bc", BCS, ids=lambda b: "".join(map(str, b)))
+@pytest.mark.parametrize("size", SIZES, ids=lambda s: "x".join(map(str, s)))
+def test_shapes_against_one_step_and_the_oracle(size, bc):
+    for source, beta in [(False, 0.0), (True, 0.6)]:
+        w = box(*size, bc, source, beta)
+        print(f"[gpu] d3q19 moments {w.name} bc={bc} source={source}", flush=True)
+        sys.stdout.flush()
+        o = run_oracle3(w)
+        for precision in (btrt.F64, btrt.F32):
+            want = None
+            for shape in [(1, 0, 0), (0, 0, 0), (2, 0, 0), (2, 1, 2), (2, 3, 4)]:
+                with btrt3.Solver3(btrt3.problem_from_workload3(w, precision=precision), w.phi0()) as s:
+                    s.set_launch(*shape)
+                    f0 = s.populations()
+                    s.step(w.steps)
+                    got = (f0, s.populations(), s.field())
+                if want is None:
+                    want = got
+                    if precision == btrt.F64:
+                        assert normwise(got[0], run_oracle3(w, 0).f) <= 1e-15
+                        assert normwise(got[1], o.f) <= 1e-12 and normwise(got[2], o.phi()) <= 1e-12
+                assert all(np.array_equal(x, y) for x, y in zip(got, want)), (shape, precision)
