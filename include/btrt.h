@@ -54,7 +54,9 @@ extern "C" {
 #define BTRT_F32 1     /* populations stored and collided in FP32 (reductions stay FP64) */
 #define BTRT_F16DEV 2  /* populations stored as FP16 scaled deviations from equilibrium,
                           h = q(s (f+ - f_eq(phi))) with phi in FP32 and a power-of-two s set
-                          at create from max|phi0|; FP32 collision; single handles only */
+                          at create from max|phi0|; FP32 collision; single handles only. With k0 = 1
+                          and K2 = 1 the state is phi and two or three moments in FP32 instead (12
+                          or 16 bytes a node, against 22), in the arithmetic of BTRT_F32 */
 #define BTRT_BF16DEV 3 /* the same with BF16 deviations */
 
 #define BTRT_PERIODIC 0

@@ -128,7 +128,7 @@ CkSizes ck_sizes(const Instance& I)
 {
     CkSizes z{};
     const size_t ps = I.precision == BTRT_F64 ? 8 : 4;
-    z.f = static_cast<size_t>(I.state_planes()) * static_cast<size_t>(I.plane) * pop_bytes(I.precision);
+    z.f = static_cast<size_t>(I.state_planes()) * static_cast<size_t>(I.plane) * I.state_bytes();
     z.phi = static_cast<size_t>(I.plane) * ps;
     z.snap = static_cast<size_t>(I.nx) * I.ny * 8;
     z.wall = I.gen ? static_cast<size_t>(I.wall_entry_slots()) * ps : 0;

@@ -333,6 +333,7 @@ void fill_constants(Instance& I, SweepArgs<T>& a, const btrt_flux_t* B, const bt
     a.rr = static_cast<T>(R ? R->r : 0.0);
     a.rp = static_cast<T>(R && R->r != 0.0 ? R->p : 1.0);
     a.dpoly = r.dq[0] != 0.0 && !I.mom ? 1 : 0;
+    a.mom_16 = I.precision == BTRT_F16DEV || I.precision == BTRT_BF16DEV ? 1 : 0;
     a.mom_g = I.mom && (I.kind != kSrcNone || a.rr != T(0)) ? 1 : 0;
     a.dg = static_cast<T>(r.dq[1]);
     a.de = static_cast<T>(r.dq[2]);
@@ -366,10 +367,11 @@ int instance_setup(Instance& I, const btrt_grid_t* grid, const btrt_flux_t* B, c
     I.growth = r.growth;
     I.gen = I.gen_problem = r.gen;
     // The moment form: k0 = 1 and every second-order rate 1 leave nothing else of f+ (a term
-    // D = d(phi) I other than phi I would).
+    // D = d(phi) I other than phi I would). It serves the 16-bit formats too, as FP32 moments: phi and
+    // two or three planes of four bytes (12 or 16 bytes a node) are fewer than nine 16-bit deviations
+    // and phi (22), and nothing is rounded to 16 bits.
     const bool phi_i = r.dq[0] == 0.0 || (r.dq[1] == 1.0 && r.dq[2] == 0.0);
-    I.mom = r.k0 == 1.0 && r.K2[0] == 1.0 && r.K2[3] == 1.0 && 0.5 * (r.K2[1] + r.K2[2]) == 1.0 && phi_i &&
-            (grid->precision == BTRT_F64 || grid->precision == BTRT_F32);
+    I.mom = r.k0 == 1.0 && r.K2[0] == 1.0 && r.K2[3] == 1.0 && 0.5 * (r.K2[1] + r.K2[2]) == 1.0 && phi_i;
     I.wtab = nullptr;
     I.wall_t0 = 0;
     I.wall_limit = INT64_MAX;
@@ -582,6 +584,9 @@ SweepArgs<T> with_source_factors(const Instance& I, SweepArgs<T> a, int steps)
 
 }  // namespace
 
+// Storage format of the planes as the kernels see it: the moment form is always plain.
+static int state_format(const Instance& I) { return I.mom ? static_cast<int>(kFmtPlain) : format_of(I.precision); }
+
 int instance_launch(Instance& I, const LaunchCfg& cfg, hipStream_t s)
 {
     hipError_t e;
@@ -590,7 +595,7 @@ int instance_launch(Instance& I, const LaunchCfg& cfg, hipStream_t s)
                                  I.kmode(), cfg, s);
     else
         e = launch_sweep<float>(with_source_factors(I, sweep_args<float>(I, I.cur), cfg.steps),
-                                format_of(I.precision), I.kind, I.kmode(), cfg, s);
+                                state_format(I), I.kind, I.kmode(), cfg, s);
     if (e != hipSuccess) return hip_fail(e, "sweep launch");
     I.cur ^= 1;
     I.step += cfg.steps;
@@ -626,7 +631,7 @@ LaunchCfg instance_resolve(const Instance& I, const LaunchCfg& cfg)
 {
     if (I.precision == BTRT_F64)
         return resolve_launch<double>(sweep_args<double>(I, I.cur), kFmtPlain, I.kind, I.kmode(), cfg);
-    return resolve_launch<float>(sweep_args<float>(I, I.cur), format_of(I.precision), I.kind, I.kmode(), cfg);
+    return resolve_launch<float>(sweep_args<float>(I, I.cur), state_format(I), I.kind, I.kmode(), cfg);
 }
 
 int instance_reduce_async(Instance& I, int mode, hipStream_t s)
@@ -634,7 +639,7 @@ int instance_reduce_async(Instance& I, int mode, hipStream_t s)
     double* result = reinterpret_cast<double*>(I.mem + I.L.result);
     hipError_t e = I.precision == BTRT_F64
                        ? launch_reduce<double>(gather_args<double>(I), kFmtPlain, mode, result, s)
-                       : launch_reduce<float>(gather_args<float>(I), format_of(I.precision), mode, result, s);
+                       : launch_reduce<float>(gather_args<float>(I), state_format(I), mode, result, s);
     return e == hipSuccess ? static_cast<int>(BTRT_OK) : hip_fail(e, "reduce launch");
 }
 
@@ -655,7 +660,7 @@ int instance_gather(Instance& I, int population, double* host_out, hipStream_t s
     } else {
         GatherArgs<float> g = gather_args<float>(I);
         g.population = population;
-        e = launch_gather_field<float>(g, format_of(I.precision), s);
+        e = launch_gather_field<float>(g, state_format(I), s);
     }
     if (e != hipSuccess) return hip_fail(e, "gather launch");
     e = hipMemcpyAsync(host_out, I.mem + I.L.tmp, nn * sizeof(double), hipMemcpyDeviceToHost, s);

@@ -78,7 +78,7 @@ struct Instance {
     // wtab + (t - wall_t0) * wall_stride. Steps may advance the count up to wall_limit.
     bool gen = false;
     bool gen_problem = false;  // the problem itself selects it (not a wall schedule)
-    bool mom = false;          // the state is in the moment form (k0 = 1, K2 = 1, plain storage; btrt_mom.h)
+    bool mom = false;          // the state is in the moment form (k0 = 1, K2 = 1; btrt_mom.h)
     const char* wtab = nullptr;
     int64_t wall_t0 = 0;
     int64_t wall_limit = INT64_MAX;
@@ -103,6 +103,7 @@ struct Instance {
     }
     // Planes of a population buffer that hold the state.
     int state_planes() const { return mom ? (mom_g() ? 3 : 2) : 9; }
+    size_t state_bytes() const { return mom ? (precision == BTRT_F64 ? 8 : 4) : pop_bytes(precision); }  // per value
     bool mom_g() const { return precision == BTRT_F64 ? a64.mom_g != 0 : a32.mom_g != 0; }
     // A moment-form state whose first step is already in its planes: it changes the count alone.
     bool first_step_free() const { return mom && step == 0; }

@@ -75,6 +75,7 @@ struct SweepArgs {
     int tiles_x, tiles_y; // set by the launcher for the kernel it picks
     int rows;             // rows per strip of the strip walkers (set by the launcher)
     int edge_rows;        // moment walkers: rows of the first and last band on a grid with y walls (0: rows)
+    int mom_16;           // moment form of a handle with 16-bit storage (its reported automatic shape differs)
     int mom_g;            // moment form: the state has a g plane (a source of any kind makes g differ from phi)
     int nts;              // 1: the one-step and two-step tile kernels store non-temporally (grids
                           // much larger than the caches; the launcher picks the kernel by it)

@@ -700,7 +700,7 @@ int mom_waves_per_simd()
 }
 
 // Rows per strip so that all strips of a launch are resident at once, n to a SIMD: the launch then
-// takes about n (rows + 2K) rows of a walk, 2K of them fill, at 0.94 (K >= 6) or 0.78 of the rate
+// takes about n (rows + 2K) rows of a walk, 2K of them fill, at 0.94 (K >= 6) or 0.72 of the rate
 // where a SIMD holds a single wavefront. (FP64, measured: 4096^2, K = 7: 171 rows, two to a SIMD,
 // 335 us, 64 rows 383 us; 2048^2: 86 rows, one to a SIMD, 87.8 us, 43 rows, two, 91.3 us; 1024^2,
 // K = 4: 10 rows 19.0 us, 8 rows 22.2, 12 rows 20.3, 16 rows 23.5, 20 rows, one to a SIMD, 18.8.)
@@ -720,7 +720,7 @@ int mom_fit_rows(const SweepArgs<T>& a)
         bands = std::max<int64_t>(1, std::min<int64_t>(bands, a.ny));
         const int64_t r = (a.ny + bands - 1) / bands;
         const int64_t rounds = (strips * ((a.ny + r - 1) / r) + simds * n - 1) / (simds * n);
-        const double cost = static_cast<double>(rounds) * n * (r + 2 * K) / (n == 1 ? (K >= 6 ? 0.94 : 0.78) : 1.0);
+        const double cost = static_cast<double>(rounds) * n * (r + 2 * K) / (n == 1 ? (K >= 6 ? 0.94 : 0.72) : 1.0);
         if (rows == 0 || cost < best) {
             best = cost;
             rows = static_cast<int>(r);
@@ -765,10 +765,11 @@ LaunchCfg mom_resolve(const SweepArgs<T>& a, LaunchCfg cfg)
     const bool automatic = cfg.steps <= 0;
     if (automatic) {
         const bool deep = !GEN && nodes >= (periodic || fp64 ? (1LL << 22) : (1LL << 24));
-        cfg.steps = deep ? (fp64 && !periodic ? kAutoDeepWalls : kAutoDeep) : (nodes >= (1LL << 20) ? kAutoFuse : 1);
-        if (cfg.steps == 1) {
-            cfg.fuse = kMomSmall;
-            cfg.fit_rows = mom_fit<T, SRC, KM>(a, cfg.fuse);
+        const int use = deep ? (fp64 && !periodic ? kAutoDeepWalls : kAutoDeep) : (nodes >= (1LL << 20) ? kAutoFuse : kMomSmall);
+        cfg.steps = nodes < (1LL << 20) ? 1 : (a.mom_16 ? kAutoFuse : use);
+        if (use != cfg.steps) {
+            cfg.fuse = use;
+            cfg.fit_rows = mom_fit<T, SRC, KM>(a, use);
         }
     }
     if (cfg.steps != 2) cfg.tile = 0;
@@ -783,7 +784,7 @@ LaunchCfg mom_resolve(const SweepArgs<T>& a, LaunchCfg cfg)
     }
     if (cfg.rows <= 0) {
         const int k = GEN ? (cfg.steps >= 4 ? 4 : 2) : cfg.steps;  // the general model's longest launch
-        cfg.fit_rows = mom_fit<T, SRC, KM>(a, k);
+        if (cfg.fit_rows <= 0) cfg.fit_rows = mom_fit<T, SRC, KM>(a, k);
         cfg.rows = 8;
         if (fp64 && cfg.steps >= 6 && cfg.fit_rows >= 64) {
             cfg.rows = cfg.fit_rows;
