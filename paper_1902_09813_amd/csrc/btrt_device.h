@@ -358,6 +358,141 @@ __global__ __launch_bounds__(kBlock2) void sweep2_kernel(SweepArgs<typename F::T
     tile2<F, SRC, KM, NT>(a, tile - ty * a.tiles_x, ty, lf, lphi);
 }
 
+// ---- several time steps per launch on small grids: one node per thread -------------------------
+// A workgroup holds a region of EX x EY nodes, one per thread, in registers: it pulls them once from
+// global memory and then takes `steps` steps, passing the post-collision populations to the
+// neighbours through LDS (two buffers, one barrier per step). Every step after the first narrows the
+// valid part of the region by one node per side, so the output tile is (EX - 2 (steps - 1)) x
+// (EY - 2 (steps - 1)). The redundant nodes cost nothing while the chip is empty: a small grid is bound
+// by the latency of its launches (about 3 us each, whatever they do) and of one step, which here are
+// paid once per `steps` and without a trip through memory. Every node update is the arithmetic of
+// sweep_kernel, so the results have its bits.
+template <typename F, int SRC, int KM>
+__global__ __launch_bounds__(1024) void block_kernel(SweepArgs<typename F::T> a, int steps, int log_ex)
+{
+    using T = typename F::T;
+    constexpr bool GEN = (KM & kGen) != 0;
+    extern __shared__ __attribute__((aligned(16))) char block_lds[];
+    T* const lds = reinterpret_cast<T*>(block_lds);
+    const int E = static_cast<int>(blockDim.x), EX = 1 << log_ex, EY = E >> log_ex;
+    const int t = static_cast<int>(threadIdx.x), lx = t & (EX - 1), ly = t >> log_ex;
+    const int h = steps - 1;
+    const int tile = xcd_tile();
+    const int tyi = tile / a.tiles_x, txi = tile - tyi * a.tiles_x;
+    const int ux = txi * (EX - 2 * h) - h + lx, uy = tyi * (EY - 2 * h) - h + ly;
+    const bool xin = ux >= 0 && ux < a.nx, yin = uy >= 0 && uy < a.ny;
+    const bool node = (a.perx || xin) && (a.pery || yin);
+    const int x = a.perx ? wrap(ux, a.nx) : (xin ? ux : 0), y = a.pery ? wrap(uy, a.ny) : (yin ? uy : 0);
+    const bool out = xin && yin && lx >= h && lx < EX - h && ly >= h && ly < EY - h;
+    const int n = y * a.pitch + x;
+    const bool okxm = a.perx || x > 0, okxp = a.perx || x < a.nx - 1;
+    const bool okym = a.pery || y > 0, okyp = a.pery || y < a.ny - 1;
+    // LDS slots of the neighbours (the region's own edge reads itself: those nodes are past their use).
+    const int xm = lx > 0 ? 1 : 0, xp = lx < EX - 1 ? 1 : 0, ym = ly > 0 ? EX : 0, yp = ly < EY - 1 ? EX : 0;
+    T f[9] = {};
+    T phi = T(0);
+    if (node) {
+        F::template pull<GEN>(a, x, y, f);
+        phi = a.phi_prev[n];
+    }
+    const T tw1 = T(2) * Lat<T>::w1, tw5 = T(2) * Lat<T>::w5;
+    for (int s = 0; s < steps; ++s) {
+        if (node) {
+            const T now = collide<T, SRC, collide_mode<F, KM>()>(a, f, phi, source_at<T, SRC>(a, n, x, y, s), n);
+            if (s == steps - 1) {
+                if (out) F::template put<false>(a, n, f, now);
+            } else {
+                F::settle(a, f, now);
+            }
+            phi = now;
+        }
+        if (s == steps - 1) break;
+        T* const b = lds + (s & 1) * 9 * E + t;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) b[i * E] = f[i];
+        __syncthreads();
+        auto wv = [&](int i, bool ox, bool oy) {
+            if constexpr (GEN)
+                return table_wall(a, x, y, s + 1, i, ox, oy);
+            else
+                return side_wall(a.wall, i, ox, oy);
+        };
+        f[1] = okxm ? b[1 * E - xm] : bounce(b[3 * E], tw1, wv(1, true, false));
+        f[2] = okym ? b[2 * E - ym] : bounce(b[4 * E], tw1, wv(2, false, true));
+        f[3] = okxp ? b[3 * E + xp] : bounce(b[1 * E], tw1, wv(3, true, false));
+        f[4] = okyp ? b[4 * E + yp] : bounce(b[2 * E], tw1, wv(4, false, true));
+        f[5] = (okxm && okym) ? b[5 * E - ym - xm] : bounce(b[7 * E], tw5, wv(5, !okxm, !okym));
+        f[6] = (okxp && okym) ? b[6 * E - ym + xp] : bounce(b[8 * E], tw5, wv(6, !okxp, !okym));
+        f[7] = (okxp && okyp) ? b[7 * E + yp + xp] : bounce(b[5 * E], tw5, wv(7, !okxp, !okyp));
+        f[8] = (okxm && okyp) ? b[8 * E + yp - xm] : bounce(b[6 * E], tw5, wv(8, !okxm, !okyp));
+    }
+}
+
+// Compute units of the current device (cached per device ordinal).
+inline int device_cus()
+{
+    static int cache[64] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    if (cache[dev] <= 0) {
+        int n = 0;
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+        cache[dev] = n;
+    }
+    return cache[dev];
+}
+
+// Shape of the block kernels for a grid: regions of 16 x 16, 32 x 16 or 32 x 32 nodes and 2 .. 7 steps
+// per launch, the cheapest per step by a model of the launch fitted on gfx950 (us): `fixed` once, and
+// for every 16 wavefronts a CU is given 0.9 and steps (a + b w), w wavefronts sharing a SIMD. ring: how
+// many nodes per side the first step already narrows the region by (0: it pulls from memory).
+// Measured against it, moment form FP64 (a = 0.19, b = 0.1): 64^2 16 x 16 nodes, 6 steps 4.38 us (model
+// 4.44); 100^2 32 x 16, 6 steps 5.22 (5.04); 400^2 16 x 16, 4 steps 9.9 (9.8).
+struct BlockShape {
+    int threads = 0, log_ex = 0, steps = 0;
+};
+
+inline int block_log_ex(int threads) { return threads == 256 ? 4 : 5; }
+
+inline BlockShape block_shape(int nx, int ny, int ring, double fixed, double a, double b, bool one_round)
+{
+    BlockShape best;
+    double best_t = 0;
+    const double cus = device_cus();
+    for (int threads : {256, 512, 1024}) {
+        const int le = block_log_ex(threads);
+        for (int s = 2; s <= kMaxFuse; ++s) {
+            const int tx = (1 << le) - 2 * (s - 1 + ring), ty = (threads >> le) - 2 * (s - 1 + ring);
+            if (tx < 2 || ty < 2) break;
+            const int64_t wgs = static_cast<int64_t>((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
+            if (one_round && (threads > 256 || wgs > static_cast<int64_t>(cus) || s < 3)) continue;
+            double k = wgs > cus ? wgs / cus : 1.0;
+            if (threads == 1024) k = static_cast<double>(static_cast<int64_t>(k + 0.999));
+            const double load = k * threads / 64, rounds = load > 16 ? load / 16 : 1.0;
+            const double t = (fixed + rounds * (0.9 + s * (a + b * (load < 16 ? load : 16.0) / 4))) / s;
+            if (best.steps == 0 || t < best_t) {
+                best_t = t;
+                best = BlockShape{threads, le, s};
+            }
+        }
+    }
+    return best;
+}
+
+// Launches `steps` steps on regions of (1 << log_ex) x (threads >> log_ex) nodes.
+template <typename F, int SRC, int KM>
+hipError_t block_launch(SweepArgs<typename F::T> a, int steps, int threads, int log_ex, hipStream_t s)
+{
+    using T = typename F::T;
+    const int tx = (1 << log_ex) - 2 * (steps - 1), ty = (threads >> log_ex) - 2 * (steps - 1);
+    if (steps < 1 || steps > kMaxFuse || tx < 1 || ty < 1) return hipErrorInvalidValue;
+    a.tiles_x = (a.nx + tx - 1) / tx;
+    a.tiles_y = (a.ny + ty - 1) / ty;
+    const unsigned grid = static_cast<unsigned>(a.tiles_x) * static_cast<unsigned>(a.tiles_y);
+    hipLaunchKernelGGL((block_kernel<F, SRC, KM>), dim3(grid), dim3(threads), 2 * 9 * threads * sizeof(T), s, a, steps, log_ex);
+    return hipGetLastError();
+}
+
 // ---- K time steps per launch: strip walkers ------------------------------------------------
 // One wavefront owns a strip of W = 64 - 2(K-1) columns by a.rows rows and walks down it one row
 // per iteration; its 64 lanes hold the strip plus K-1 halo columns on each side. In iteration r,
@@ -919,20 +1054,6 @@ __global__ __launch_bounds__(kWave) void batchw_kernel(const BatchEntry<T>* __re
     }
 }
 
-// Compute units of the current device (cached per device ordinal).
-inline int device_cus()
-{
-    static int cache[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    if (cache[dev] <= 0) {
-        int n = 0;
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-        cache[dev] = n;
-    }
-    return cache[dev];
-}
-
 // Resident wavefronts per CU of one walker instantiation (its registers decide).
 template <typename F, int SRC, int KP, int K>
 int walk_waves_per_cu()
@@ -1007,6 +1128,16 @@ LaunchCfg resolve_variant(const SweepArgs<typename F::T>& a, LaunchCfg cfg)
         const bool fp64 = sizeof(typename F::T) == 8, periodic = a.perx && a.pery;
         const bool deep = plain_format<F>() && (KP & kGen) == 0 && nodes >= (periodic || fp64 ? (1LL << 22) : (1LL << 24));
         cfg.steps = deep ? (fp64 && !periodic ? kAutoDeepWalls : kAutoDeep) : (nodes >= (1LL << 20) ? kAutoFuse : 1);
+        if (cfg.steps == 1) {
+            // Below 2^20 nodes several steps per launch by the block kernel (us a step, one step per launch
+            // and blocks, FP64 constant K1: 64^2 3.6 and 1.04, 300^2 4.6 and 1.9, 700^2 12.7 and 6.6,
+            // 1000^2 25 and 11.5); the general model's four powers make the redundant nodes dear, so there
+            // only while one round of small regions holds the grid (120^2 5.9 and 4.3, 300^2 7.5 and 8.1).
+            const BlockShape b = (KP & kGen) != 0 ? block_shape(a.nx, a.ny, 0, 2.5, 2.0, 1.4, true)
+                                                  : block_shape(a.nx, a.ny, 0, 2.5, fp64 ? 0.34 : 0.3, fp64 ? 0.18 : 0.15, false);
+            cfg.fuse = b.steps;
+            cfg.block = b.threads;
+        }
     }
     if (cfg.steps != 2) cfg.tile = 0;
     if (cfg.steps == 1) {  // rows: tile height of the one-step kernel
@@ -1049,6 +1180,7 @@ template <typename F, int SRC, int KP>
 hipError_t sweep_variant(SweepArgs<typename F::T> a, LaunchCfg cfg, hipStream_t s)
 {
     using T = typename F::T;
+    if (cfg.block > 0 && cfg.steps > 1) return block_launch<F, SRC, KP>(a, cfg.steps, cfg.block, block_log_ex(cfg.block), s);
     cfg = resolve_variant<F, SRC, KP>(a, cfg);
     if (cfg.steps < 1 || cfg.steps > kMaxFuse || cfg.rows < 0 || (cfg.steps >= 2 && !cfg.tile && cfg.rows < 1) ||
         (cfg.steps == 1 && (cfg.rows < 1 || cfg.rows > kMaxBlock1 / kTileX || (cfg.rows & (cfg.rows - 1)))) ||

@@ -617,7 +617,7 @@ int instance_steps(Instance& I, const LaunchCfg& want, int64_t n, hipStream_t s)
     for (int64_t i = 0; i < n;) {
         LaunchCfg k = c;
         k.steps = static_cast<int>(std::min<int64_t>(per, n - i));
-        if (I.mom && I.gen) k.steps = k.steps >= 4 ? 4 : (k.steps >= 2 ? 2 : 1);  // the launches it has
+        if (I.mom && I.gen && k.block == 0) k.steps = k.steps >= 4 ? 4 : (k.steps >= 2 ? 2 : 1);  // the launches it has
         if (k.steps != 2) k.tile = 0;
         if (k.steps == 1 && c.steps != 1) k.rows = k.group = 0;  // the one-step kernel's own tiles
         int rc = instance_launch(I, k, s);

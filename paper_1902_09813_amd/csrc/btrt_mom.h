@@ -595,6 +595,76 @@ __global__ __launch_bounds__(kWave* kWalkGroup) void mom_walk_kernel(SweepArgs<T
     mom_strip_any<T, SRC, KM, K, C, WALLS>(a, sx, ys, ye, static_cast<int>(threadIdx.x % kWave));
 }
 
+// ---- several steps per launch on small grids: one node per thread -------------------------------
+// As block_kernel (btrt_device.h): x neighbours by lane shifts, rows through LDS (A+-, C+- of every node,
+// four values instead of nine). Each step narrows the valid region by one node per side.
+template <typename T, bool SRC, int KM>
+__global__ __launch_bounds__(1024) void mom_block_kernel(SweepArgs<T> a, int steps, int log_ex)
+{
+    constexpr int SRCG = mom_srcg<SRC, KM>();
+    constexpr bool GEN = (KM & kGen) != 0;
+    extern __shared__ __attribute__((aligned(16))) char block_lds[];
+    T* const lds = reinterpret_cast<T*>(block_lds);
+    const int E = static_cast<int>(blockDim.x), EX = 1 << log_ex, EY = E >> log_ex;
+    const int t = static_cast<int>(threadIdx.x), lx = t & (EX - 1), ly = t >> log_ex;
+    const int tile = xcd_tile();
+    const int tyi = tile / a.tiles_x, txi = tile - tyi * a.tiles_x;
+    const int ux = txi * (EX - 2 * steps) - steps + lx, uy = tyi * (EY - 2 * steps) - steps + ly;
+    const bool xin = ux >= 0 && ux < a.nx, yin = uy >= 0 && uy < a.ny;
+    const bool node = (a.perx || xin) && (a.pery || yin);
+    const int x = a.perx ? wrap(ux, a.nx) : (xin ? ux : 0), y = a.pery ? wrap(uy, a.ny) : (yin ? uy : 0);
+    const bool out = xin && yin && lx >= steps && lx < EX - steps && ly >= steps && ly < EY - steps;
+    const int n = y * a.pitch + x;
+    const bool oxm = !a.perx && x == 0, oxp = !a.perx && x == a.nx - 1;
+    const bool oym = !a.pery && y == 0, oyp = !a.pery && y == a.ny - 1;
+    const bool edge = node && (oxm || oxp || oym || oyp);
+    const int below = ly > 0 ? EX : 0, above = ly < EY - 1 ? EX : 0;
+    MomState<T> v{T(0), T(0), T(0), T(0)};
+    T src = T(0);
+    if (node) {
+        v.phi = a.phi_prev[n];
+        v.qx = a.fin[kMomQx * a.plane + n];
+        v.qy = a.fin[kMomQy * a.plane + n];
+        v.g = SRCG == 1 || (SRCG == 2 && a.mom_g) ? a.fin[kMomG * a.plane + n] : v.phi;
+        if constexpr (SRC) src = mom_source(a, n, x, y);
+    }
+    for (int s = 0; s < steps; ++s) {
+        MomNode<T> N = mom_node(v.g, v.qx, v.qy);
+        if (!node) N = MomNode<T>{};
+        const MomRow<T> R = mom_row(N.gs, N.r, lane_shift<kShr1>(N.p), lane_shift<kShr1>(N.r), lane_shift<kShl1>(N.m),
+                                    lane_shift<kShl1>(N.r));
+        T* const b = lds + (s & 1) * 4 * E + t;
+        b[0 * E] = R.Ap;
+        b[1 * E] = R.Cp;
+        b[2 * E] = R.Am;
+        b[3 * E] = R.Cm;
+        __syncthreads();
+        const T Ap = b[0 * E - below], Cp = b[1 * E - below], Am = b[2 * E + above], Cm = b[3 * E + above];
+        MomPart<T> f = mom_part(R.H, R.J, Ap, Cp);
+        f.phi = f.phi + Am;
+        f.jx = f.jx + Cm;
+        f.jy = f.jy - Am;
+        if (edge)
+            mom_walls(N, oxm, oxp, oym, oyp,
+                      [&](int i, bool ox, bool oy) { return mom_wall<T, GEN>(a, x, y, s, i, ox, oy); }, f);
+        v = mom_collide<T, SRC, KM>(a, f, v.phi, SRC ? src * a.sfac[s] : T(0), n);
+    }
+    if (out) mom_put<T, SRC, KM>(a, n, v);
+}
+
+// Launches `steps` steps on regions of (1 << log_ex) x (threads >> log_ex) nodes.
+template <typename T, bool SRC, int KM>
+hipError_t mom_block_launch(SweepArgs<T> a, int steps, int threads, int log_ex, hipStream_t s)
+{
+    const int tx = (1 << log_ex) - 2 * steps, ty = (threads >> log_ex) - 2 * steps;
+    if (steps < 1 || steps > kMaxFuse || tx < 1 || ty < 1) return hipErrorInvalidValue;
+    a.tiles_x = (a.nx + tx - 1) / tx;
+    a.tiles_y = (a.ny + ty - 1) / ty;
+    const unsigned grid = static_cast<unsigned>(a.tiles_x) * static_cast<unsigned>(a.tiles_y);
+    hipLaunchKernelGGL((mom_block_kernel<T, SRC, KM>), dim3(grid), dim3(threads), 2 * 4 * threads * sizeof(T), s, a, steps, log_ex);
+    return hipGetLastError();
+}
+
 // ---- many instances in one launch (see the population form's batched kernels) ---------------
 template <typename T>
 __global__ __launch_bounds__(kBlock) void mom_batch1_kernel(const BatchEntry<T>* __restrict__ ent,
@@ -771,6 +841,18 @@ LaunchCfg mom_resolve(const SweepArgs<T>& a, LaunchCfg cfg)
             cfg.fuse = use;
             cfg.fit_rows = mom_fit<T, SRC, KM>(a, use);
         }
+        // Small grids by the block kernel (us a step, four-step walkers and blocks: FP64 64^2 1.35 and 0.73,
+        // 256^2 1.60 and 1.11, 512^2 2.39 and 2.27, 700^2 2.91 and 3.50; with walls 64^2 2.40 and 0.86, 512^2
+        // 3.94 and 2.27, 700^2 3.90 and 3.65; FP32 512^2 2.04 and 1.58, 700^2 2.51 and 2.34, 1000^2 3.37 and
+        // 4.26); the general model as in the population form.
+        if (nodes <= (fp64 && periodic ? (1LL << 18) : (1LL << 19))) {
+            const BlockShape b = GEN ? block_shape(a.nx, a.ny, 1, 2.5, 2.0, 1.4, true)
+                                     : block_shape(a.nx, a.ny, 1, 1.8, fp64 ? 0.19 : 0.16, fp64 ? 0.1 : 0.08, false);
+            if (b.steps > 0) {
+                cfg.fuse = b.steps;
+                cfg.block = b.threads;
+            }
+        }
     }
     if (cfg.steps != 2) cfg.tile = 0;
     if (cfg.steps == 1) {
@@ -803,11 +885,13 @@ LaunchCfg mom_resolve(const SweepArgs<T>& a, LaunchCfg cfg)
     return cfg;
 }
 
-// One launch of cfg.steps (1 .. 7; with the general model 1, 2 or 4) steps.
+// One launch of cfg.steps (1 .. 7; with the general model 1, 2 or 4, or up to 7 in blocks) steps.
 template <typename T, bool SRC, int KM>
 hipError_t mom_variant(const SweepArgs<T>& a, const LaunchCfg& cfg, hipStream_t s)
 {
     if (cfg.steps < 1 || cfg.steps > kMaxFuse) return hipErrorInvalidValue;
+    if (cfg.block > 0 && cfg.steps > 1)
+        return mom_block_launch<T, SRC, KM>(a, cfg.steps, cfg.block, block_log_ex(cfg.block), s);
     int rows = cfg.fit_rows > 0 ? cfg.fit_rows : cfg.rows;
     if (cfg.steps == 1) {
         rows = cfg.rows;
