@@ -171,6 +171,7 @@ struct btrt3 {
     bool own_stream = false;
     char* mem = nullptr;
     Layout3 L{};
+    StagingUser staging;
     int precision = BTRT_F64;
     int nx = 0, ny = 0, nz = 0, pitch = 0;
     bool src = false, k1_per_node = false;
@@ -413,8 +414,7 @@ int gather_sync(btrt3* h, int population, double* host_out)
         g.population = population;
         e = launch3_gather<float>(g, h->stream);
     }
-    if (e == hipSuccess) e = hipMemcpyAsync(host_out, h->mem + h->L.tmp, nn * sizeof(double), hipMemcpyDeviceToHost, h->stream);
-    if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+    if (e == hipSuccess) e = copy_to_host(host_out, h->mem + h->L.tmp, nn * sizeof(double), h->device, h->stream);
     return e == hipSuccess ? static_cast<int>(BTRT_OK) : hip_fail(e, "field read");
 }
 

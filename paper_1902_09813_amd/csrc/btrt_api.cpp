@@ -25,7 +25,9 @@ struct btrt {
     bool own_mem = false;
     int check_interval = 1000;
     btrtk::LaunchCfg launch{};  // requested launch shape (zero fields: automatic)
-    void* wsched = nullptr;     // device wall schedule of btrt_set_walls (owned)
+    void* wsched = nullptr;     // device wall schedule of btrt_set_walls (owned), of wsched_bytes bytes
+    size_t wsched_bytes = 0;
+    StagingUser staging;
     Instance inst;
 };
 
@@ -253,6 +255,7 @@ int btrt_restore(btrt_t* h, const void* buf, size_t bytes)
     I.gen = wall != 0;
     I.wtab = wmem ? static_cast<const char*>(wmem) : (wall ? I.mem + I.L.wall0 : nullptr);
     h->wsched = wmem;
+    h->wsched_bytes = wmem ? wall : 0;
     I.wall_t0 = hd.step;
     I.wall_stride = 0;
     I.wall_limit = wmem ? hd.step : INT64_MAX;
@@ -325,6 +328,7 @@ int btrt_create(const btrt_grid_t* grid, const btrt_flux_t* B, const btrt_diff_t
                     h->own_mem = true;
                 }
             }
+            h->inst.device = h->device;
             if (rc == BTRT_OK) rc = instance_setup(h->inst, grid, B, K, R, bc, r, phi0, h->mem, h->stream);
         }
     }
@@ -359,7 +363,8 @@ int btrt_set_walls(btrt_t* h, const double* values, int64_t steps)
     const bool wall_side[4] = {!I.perx, !I.perx, !I.pery, !I.pery};
     const int64_t sx = 2LL * I.ny + 1, sy = 2LL * I.nx + 1;
     const int64_t side_begin[5] = {0, sx, 2 * sx, 2 * sx + sy, P};
-    for (int64_t k = 0; k < steps; ++k)
+    const bool finite = all_finite(values, static_cast<size_t>(steps) * P);
+    for (int64_t k = 0; k < steps && !finite; ++k)  // say where, unless it is a periodic side's entry
         for (int q = 0; q < 4; ++q) {
             if (!wall_side[q]) continue;
             for (int64_t e = side_begin[q]; e < side_begin[q + 1]; ++e)
@@ -371,29 +376,35 @@ int btrt_set_walls(btrt_t* h, const double* values, int64_t steps)
     const size_t bytes = static_cast<size_t>(S) * static_cast<size_t>(steps + 1) * es;
     DeviceGuard g(h->device);
     if (g.status() != hipSuccess) return hip_fail(g.status(), "hipSetDevice");
-    void* mem = nullptr;
-    if (hipMalloc(&mem, bytes) != hipSuccess) {
+    // The table of an earlier call serves again where it is large enough: what it still feeds is ahead
+    // of the new values on the stream.
+    void* mem = h->wsched;
+    const bool fresh = !mem || h->wsched_bytes < bytes;
+    if (fresh && hipMalloc(&mem, bytes) != hipSuccess) {
         (void)hipGetLastError();
         return fail(BTRT_E_NOMEM, "hipMalloc of %zu bytes for the wall schedule failed", bytes);
     }
     char* dst = static_cast<char*>(mem);
     // Entry 0: the values the next pull reads (the step that ends at the current count), from
     // the current table, or the per-side constants the populations were initialised with.
-    hipError_t e;
+    hipError_t e = hipSuccess;
     if (I.gen && I.wtab) {
         const char* cur = I.wtab + static_cast<size_t>(I.step - I.wall_t0) * I.wall_stride * es;
-        e = hipMemcpyAsync(dst, cur, static_cast<size_t>(S) * es, hipMemcpyDeviceToDevice, h->stream);
-        if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
+        if (cur != dst) e = hipMemcpyAsync(dst, cur, static_cast<size_t>(S) * es, hipMemcpyDeviceToDevice, h->stream);
     } else {
         e = upload_wall_entry(I, dst, h->stream);
     }
     if (e == hipSuccess) e = upload_wall_values(I, values, static_cast<size_t>(steps), dst + S * es, h->stream);
     if (e != hipSuccess) {
-        (void)hipFree(mem);
+        (void)hipStreamSynchronize(h->stream);
+        if (fresh) (void)hipFree(mem);
         return hip_fail(e, "wall schedule upload");
     }
-    if (h->wsched) (void)hipFree(h->wsched);  // the stream is idle: nothing reads it any more
-    h->wsched = mem;
+    if (fresh) {
+        if (h->wsched) (void)hipFree(h->wsched);  // the stream is idle: nothing reads it any more
+        h->wsched = mem;
+        h->wsched_bytes = bytes;
+    }
     I.gen = true;
     I.wtab = dst;
     I.wall_t0 = I.step;

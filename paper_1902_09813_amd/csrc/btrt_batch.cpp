@@ -17,6 +17,7 @@ struct btrt_batch {
     hipStream_t stream = nullptr;
     bool own_stream = false;
     char* arena = nullptr;
+    StagingUser staging;
     std::vector<Instance> inst;
     Group group;
 };
@@ -92,6 +93,7 @@ int btrt_batch_create(int32_t n, const btrt_problem_t* problems, int32_t device,
         if (rc == BTRT_OK) rc = group_init(b->group, device, b->stream, precision, n);
         for (int i = 0; i < n && rc == BTRT_OK; ++i) {
             const btrt_problem_t& p = problems[i];
+            b->inst[i].device = device;
             rc = instance_setup(b->inst[i], &p.grid, &p.B, &p.K, &p.R, &p.bc, res[i], p.phi0, b->arena + offs[i],
                                 b->stream);
             b->group.inst.push_back(&b->inst[i]);

@@ -267,12 +267,25 @@ void fill_info(const btrt_grid_t* g, const Resolved& r, int src_kind, btrt_info_
 }
 
 
+bool all_finite(const double* v, size_t n)
+{
+    constexpr uint64_t kExp = 0x7ff0000000000000ull;
+    uint64_t bad = 0;
+    for (size_t k = 0; k < n; ++k) {  // no early exit: the loop vectorises
+        uint64_t u;
+        std::memcpy(&u, v + k, sizeof(u));
+        bad |= (u & kExp) == kExp ? 1 : 0;
+    }
+    return bad == 0;
+}
+
 int validate_phi0(const btrt_grid_t* grid, const double* phi0)
 {
     if (!phi0) return fail(BTRT_E_INVAL, "phi0 is NULL");
     const size_t nn = static_cast<size_t>(grid->nx) * grid->ny;
-    for (size_t k = 0; k < nn; ++k)
-        if (!is_finite(phi0[k])) return fail(BTRT_E_INVAL, "non-finite phi0 at node %zu", k);
+    if (!all_finite(phi0, nn))
+        for (size_t k = 0; k < nn; ++k)
+            if (!is_finite(phi0[k])) return fail(BTRT_E_INVAL, "non-finite phi0 at node %zu", k);
     return BTRT_OK;
 }
 
@@ -529,8 +542,46 @@ double constant_sample(const Instance& I, size_t q)
 }
 }  // namespace
 
+namespace {
+// Rows of samples into wall-table entries, packed whole rows at a time into the two halves of a pinned
+// staging buffer.
+template <typename T>
+hipError_t upload_rows(const Instance& I, const double* v, size_t rows, char* dst, char* pinned, size_t bytes, hipStream_t s)
+{
+    const size_t P = static_cast<size_t>(I.wall_entry_values()), S = static_cast<size_t>(I.wall_entry_slots());
+    const size_t half = bytes / 2, fit = half / (S * sizeof(T));
+    hipError_t e = hipSuccess;
+    int use = 0;
+    for (size_t at = 0; at < rows && e == hipSuccess; at += fit, use ^= 1) {
+        if (at >= 2 * fit) e = hipStreamSynchronize(s);  // the copy out of this half has ended
+        if (e != hipSuccess) break;
+        const size_t m = std::min(fit, rows - at);
+        T* const out = reinterpret_cast<T*>(pinned + use * half);
+        for (size_t r = 0; r < m; ++r) {
+            const double* row = v + (at + r) * P;
+            T* const o = out + r * S;
+            for (size_t q = 0; q < P; ++q) o[q] = static_cast<T>(row[q]);
+            for (size_t q = P; q < S; ++q) o[q] = wall_slot<T>(I, [row](size_t k) { return row[k]; }, q);
+        }
+        e = hipMemcpyAsync(dst + at * S * sizeof(T), out, m * S * sizeof(T), hipMemcpyHostToDevice, s);
+    }
+    const hipError_t w = hipStreamSynchronize(s);
+    return e == hipSuccess ? w : e;
+}
+}  // namespace
+
 hipError_t upload_wall_values(const Instance& I, const double* v, size_t rows, char* dst, hipStream_t s)
 {
+    const size_t es = I.precision == BTRT_F64 ? 8 : 4, entry = static_cast<size_t>(I.wall_entry_slots()) * es;
+    size_t bytes = 0;
+    char* const pinned = I.device >= 0 ? static_cast<char*>(staging_get(&bytes)) : nullptr;
+    if (pinned && bytes / 2 >= entry) {
+        const hipError_t e = I.precision == BTRT_F64 ? upload_rows<double>(I, v, rows, dst, pinned, bytes, s)
+                                                     : upload_rows<float>(I, v, rows, dst, pinned, bytes, s);
+        staging_put(pinned);
+        return e;
+    }
+    staging_put(pinned);
     auto r = [v](size_t k) { return v[k]; };
     return I.precision == BTRT_F64 ? upload_entries<double>(I, r, rows, dst, s) : upload_entries<float>(I, r, rows, dst, s);
 }
@@ -634,6 +685,13 @@ LaunchCfg instance_resolve(const Instance& I, const LaunchCfg& cfg)
     return resolve_launch<float>(sweep_args<float>(I, I.cur), state_format(I), I.kind, I.kmode(), cfg);
 }
 
+hipError_t instance_download(const Instance& I, void* dst, const void* src, size_t bytes, hipStream_t s)
+{
+    if (I.device >= 0) return copy_to_host(dst, src, bytes, I.device, s);
+    const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+    return e == hipSuccess ? hipStreamSynchronize(s) : e;
+}
+
 int instance_reduce_async(Instance& I, int mode, hipStream_t s)
 {
     double* result = reinterpret_cast<double*>(I.mem + I.L.result);
@@ -663,10 +721,8 @@ int instance_gather(Instance& I, int population, double* host_out, hipStream_t s
         e = launch_gather_field<float>(g, state_format(I), s);
     }
     if (e != hipSuccess) return hip_fail(e, "gather launch");
-    e = hipMemcpyAsync(host_out, I.mem + I.L.tmp, nn * sizeof(double), hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync");
-    e = hipStreamSynchronize(s);
-    return e == hipSuccess ? static_cast<int>(BTRT_OK) : hip_fail(e, "hipStreamSynchronize");
+    e = instance_download(I, host_out, I.mem + I.L.tmp, nn * sizeof(double), s);
+    return e == hipSuccess ? static_cast<int>(BTRT_OK) : hip_fail(e, "field copy");
 }
 
 }  // namespace btrth

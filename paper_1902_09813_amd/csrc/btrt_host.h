@@ -5,6 +5,7 @@
 
 #include "btrt.h"
 #include "btrt_internal.h"
+#include "btrt_transfer.h"
 
 #include <hip/hip_runtime.h>
 
@@ -58,6 +59,7 @@ struct Resolved {
 
 int validate(const btrt_grid_t* grid, const btrt_flux_t* B, const btrt_diff_t* K, const btrt_dterm_t* D,
              const btrt_source_t* R, const btrt_bc_t* bc, const btrt_relax_t* relax, Resolved* res);
+bool all_finite(const double* v, size_t n);
 // Also rejects a NULL or non-finite phi0.
 int validate_phi0(const btrt_grid_t* grid, const double* phi0);
 void fill_info(const btrt_grid_t* g, const Resolved& r, int src_kind, btrt_info_t* info);
@@ -66,6 +68,7 @@ void fill_info(const btrt_grid_t* g, const Resolved& r, int src_kind, btrt_info_
 // phi(t-1) in phi[cur].
 // K1 mode of the kernels: constant, A0 (1 + beta phi^2), or A0(x) (1 + beta phi^2).
 struct Instance {
+    int device = -1;      // device whose large arrays are read through staging memory (-1: none are)
     int nx = 0, ny = 0, pitch = 0, precision = 0;
     int kind = 0;         // btrtk::SrcKind of the source
     bool k1_per_node = false;
@@ -146,6 +149,8 @@ int instance_steps(Instance& I, const btrtk::LaunchCfg& want, int64_t n, hipStre
 btrtk::LaunchCfg instance_resolve(const Instance& I, const btrtk::LaunchCfg& cfg);
 // Enqueues the two-pass reduction (residual or error) into I's result slot (no sync).
 int instance_reduce_async(Instance& I, int mode, hipStream_t s);
+// Copies device memory to a host array; returns when complete.
+hipError_t instance_download(const Instance& I, void* dst, const void* src, size_t bytes, hipStream_t s);
 // Copies I's result slot to out (async).
 int instance_result_async(const Instance& I, double out[btrtk::kReducePartials], hipStream_t s);
 // phi(t) (population < 0) or f_i(t) into a host array; synchronises.

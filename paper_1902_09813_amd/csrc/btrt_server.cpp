@@ -116,6 +116,7 @@ struct btrt_server {
     int check_interval = 1000;
     char* mem = nullptr;
     size_t mem_bytes = 0;
+    StagingUser staging;
     Arena arena;
     Group group;
     int64_t next_id = 1;
@@ -184,6 +185,7 @@ int admit(btrt_server* s)
         r.off = off;
         btrt_source_t R = r.R;
         if (R.kind == BTRT_SRC_FIELD) R.field = r.field.data();
+        r.inst.device = s->device;
         int rc = instance_setup(r.inst, &r.grid, &r.B, &r.K, &R, &r.bc, r.res, r.phi0.data(), s->mem + off, s->stream);
         if (rc != BTRT_OK) {
             s->arena.release(off, r.bytes);
