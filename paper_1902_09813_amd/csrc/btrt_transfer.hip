@@ -143,16 +143,16 @@ hipError_t copy_to_host(void* dst, const void* src, size_t bytes, int device, hi
 {
     char* const host = static_cast<char*>(dst);
     const char* const dev = static_cast<const char*>(src);
-    // A copy that would not occupy two threads, or whose words the kernel could not move, is left to the
-    // runtime's own path.
+    // Words the kernel could not move are left to the runtime's own path (64^2 FP64, the whole read: 33 us
+    // by that, 19 by the kernel; 500^2 126 and 90 us).
     const bool words = bytes % 8 == 0 && reinterpret_cast<uintptr_t>(dev) % 16 == 0;
     size_t got = 0;
-    char* const set = words && bytes >= 2 * kPerThread ? static_cast<char*>(staging_get(&got)) : nullptr;
+    char* const set = words ? static_cast<char*>(staging_get(&got)) : nullptr;
     if (!set) {
         const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
         return e == hipSuccess ? hipStreamSynchronize(s) : e;
     }
-    const int want = static_cast<int>(std::min<size_t>(kThreads, bytes / kPerThread));
+    const int want = static_cast<int>(std::max<size_t>(1, std::min<size_t>(kThreads, bytes / kPerThread)));
     hipError_t err[kThreads] = {};
     std::thread pool[kThreads];
     int started = 1;  // the calling thread is the first

@@ -1,5 +1,5 @@
-"""Reads of fields that go through the pinned staging buffers (2 MiB and more): sizes that leave a last word
-and a short chunk, sizes on both sides of the threshold, and several threads reading at once."""
+"""Reads of fields through the pinned staging buffers: sizes that leave a last word and a short chunk, sizes
+for one and for several copying threads, and several threads reading at once."""
 
 import threading
 
@@ -12,7 +12,7 @@ from paper_1902_09813_amd import workloads as W
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("size", [(511, 511), (513, 513), (1021, 1027), (1500, 1999)], ids=lambda s: f"{s[0]}x{s[1]}")
+@pytest.mark.parametrize("size", [(1, 1), (3, 5), (257, 255), (511, 511), (513, 513), (1021, 1027), (1500, 1999)], ids=lambda s: f"{s[0]}x{s[1]}")
 def test_field_at_step_zero_is_phi0(size):
     # At step 0 phi is phi0 exactly (k0 = K2 = 1 in FP64), so the read itself is checked.
     print(f"[gpu] read {size}", flush=True)
