@@ -113,7 +113,8 @@ int btrt3_step(btrt3_t* h, int64_t n);
  *                     chunk of planes: step 1 of each plane goes to LDS, step 2 of the plane below
  *                     is computed from it, so the state is read and written once per two steps.
  *                     With k0 = 1 and K2 = 1 the automatic shape (0) takes the steps per launch that
- *                     suit the moments such a state is kept as; what is reported stays as above
+ *                     suit the moments such a state is kept as, and with a Dirichlet face one step,
+ *                     which is faster there; what is reported stays as above
  *   z_chunk           two-step launches: output planes per workgroup (0: automatic, the chunk of
  *                     16 .. 64 planes that needs the fewest rounds of resident workgroups times
  *                     planes walked, so the launch's last round is nearly full)

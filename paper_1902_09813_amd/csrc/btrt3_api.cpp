@@ -509,8 +509,14 @@ int btrt3_step(btrt3_t* h, int64_t n)
         const int rc = mom_steps(h, c, n);
         return rc == BTRT_OK ? ok() : rc;
     }
+    // With Dirichlet faces the automatic shape runs one step per launch: the bounced links of two levels
+    // do not fit the registers (us a step with one and two: 160 x 150 x 140 FP64 206 and 609, FP32 104
+    // and 151; 256^3 1049 and 2997, 520 and 716; periodic 200 and 127, 104 and 73).
+    const int* per = h->precision == BTRT_F64 ? h->a64.per : h->a32.per;
+    const bool faces = !(per[0] && per[1] && per[2]);
+    const bool pairs = c.steps_per_launch == 2 && !(faces && h->launch.steps_per_launch == 0);
     for (int64_t s = 0; s < n;) {
-        const bool two = c.steps_per_launch == 2 && n - s >= 2;
+        const bool two = pairs && n - s >= 2;
         const bool f64 = h->precision == BTRT_F64;
         hipError_t e;
         if (two)

@@ -35,6 +35,7 @@ struct Sweep3 {
     T q2[6];            // K2 rates (k2_11, k2_12s, k2_13s, k2_22, k2_23s, k2_33), off-diagonals
                         // symmetrised (Eq. (100))
     int tiles_x, tiles_y;
+    int row;            // one step per launch: lanes a row takes (launch3_sweep)
     int nts;            // 1: the one-step kernel stores non-temporally (the launcher picks it)
     int zc;             // two-step kernel: output planes per workgroup
 };

@@ -24,9 +24,7 @@
 namespace btrt3k {
 namespace {
 
-constexpr int kTileX = 64;
-constexpr int kTileY = 4;
-constexpr int kBlock = kTileX * kTileY;
+constexpr int kBlock = 256;
 
 // D3Q19 velocities in the column order of C in Eq. (86), and the opposite of each.
 __host__ __device__ constexpr int cxv(int i)
@@ -86,42 +84,50 @@ __device__ __forceinline__ void store(T* p, T v)
         *p = v;
 }
 
-// Step 1: f_i(x, t) for all 19 directions at node (x, y, z).
+// Step 1: f_i(x, t) for all 19 directions at node (x, y, z). A wavefront of interior nodes takes constant
+// offsets; one with nodes at the box's edge (on a narrow box every one: 64 nodes reach from row to row)
+// selects each direction's offset and plane (the neighbour, wrapped, or beyond a Dirichlet face the node's
+// own opposite population) and then sets the bounced links, so no lane waits for another's path.
 template <typename T>
 __device__ __forceinline__ void pull3(const Sweep3<T>& a, int x, int y, int z, T f[kQ])
 {
-    const int64_t p = a.plane;
+    const int p = static_cast<int>(a.plane);  // 19 planes stay below 2^31 elements
     const int n = z * a.slab + y * a.pitch + x;
-    if (x > 0 && x < a.nx - 1 && y > 0 && y < a.ny - 1 && z > 0 && z < a.nz - 1) {
+    const bool xl = x == 0, xh = x == a.nx - 1, yl = y == 0, yh = y == a.ny - 1, zl = z == 0, zh = z == a.nz - 1;
+    const bool edge = xl || xh || yl || yh || zl || zh;
+    if (__builtin_amdgcn_ballot_w64(edge) == 0) {
 #pragma unroll
         for (int i = 0; i < kQ; ++i) f[i] = a.fin[i * p + n - (cxv(i) + cyv(i) * a.pitch + czv(i) * a.slab)];
         return;
     }
+    const bool out[6] = {xl && !a.per[0], xh && !a.per[0], yl && !a.per[1], yh && !a.per[1], zl && !a.per[2],
+                         zh && !a.per[2]};
+    // Offset of the neighbour a positive (negative) velocity component comes from.
+    const int xm = xl ? a.nx - 1 : -1, xp = xh ? 1 - a.nx : 1;
+    const int ym = yl ? (a.ny - 1) * a.pitch : -a.pitch, yp = yh ? (1 - a.ny) * a.pitch : a.pitch;
+    const int zm = zl ? (a.nz - 1) * a.slab : -a.slab, zp = zh ? (1 - a.nz) * a.slab : a.slab;
+    auto crosses = [&](int i) {
+        return (cxv(i) > 0 && out[0]) || (cxv(i) < 0 && out[1]) || (cyv(i) > 0 && out[2]) || (cyv(i) < 0 && out[3]) ||
+               (czv(i) > 0 && out[4]) || (czv(i) < 0 && out[5]);
+    };
 #pragma unroll
     for (int i = 0; i < kQ; ++i) {
-        int xs = x - cxv(i), ys = y - cyv(i), zs = z - czv(i);
-        int faces = 0;
-        T wsum = T(0);
-        if (xs < 0) {
-            if (a.per[0]) xs += a.nx; else { ++faces; wsum += a.wall[0]; }
-        } else if (xs >= a.nx) {
-            if (a.per[0]) xs -= a.nx; else { ++faces; wsum += a.wall[1]; }
-        }
-        if (ys < 0) {
-            if (a.per[1]) ys += a.ny; else { ++faces; wsum += a.wall[2]; }
-        } else if (ys >= a.ny) {
-            if (a.per[1]) ys -= a.ny; else { ++faces; wsum += a.wall[3]; }
-        }
-        if (zs < 0) {
-            if (a.per[2]) zs += a.nz; else { ++faces; wsum += a.wall[4]; }
-        } else if (zs >= a.nz) {
-            if (a.per[2]) zs -= a.nz; else { ++faces; wsum += a.wall[5]; }
-        }
-        if (faces == 0) {
-            f[i] = a.fin[i * p + zs * a.slab + ys * a.pitch + xs];
-        } else {
-            const T phiw = faces == 1 ? wsum : T(0.5) * wsum;
-            f[i] = fmadd(T(2) * wv<T>(i), phiw, -a.fin[oppv(i) * p + n]);
+        const int o = (cxv(i) > 0 ? xm : (cxv(i) < 0 ? xp : 0)) + (cyv(i) > 0 ? ym : (cyv(i) < 0 ? yp : 0)) +
+                      (czv(i) > 0 ? zm : (czv(i) < 0 ? zp : 0));
+        f[i] = a.fin[n + (crosses(i) ? oppv(i) * p : i * p + o)];
+    }
+    if (out[0] || out[1] || out[2] || out[3] || out[4] || out[5]) {
+#pragma unroll
+        for (int i = 1; i < kQ; ++i) {
+            const bool ox = (cxv(i) > 0 && out[0]) || (cxv(i) < 0 && out[1]);
+            const bool oy = (cyv(i) > 0 && out[2]) || (cyv(i) < 0 && out[3]);
+            const bool oz = (czv(i) > 0 && out[4]) || (czv(i) < 0 && out[5]);
+            T wsum = T(0);
+            if (ox) wsum += a.wall[cxv(i) > 0 ? 0 : 1];
+            if (oy) wsum += a.wall[cyv(i) > 0 ? 2 : 3];
+            if (oz) wsum += a.wall[czv(i) > 0 ? 4 : 5];
+            const T phiw = (ox && oy) || (ox && oz) || (oy && oz) ? T(0.5) * wsum : wsum;
+            f[i] = ox || oy || oz ? fmadd(T(2) * wv<T>(i), phiw, -f[i]) : f[i];
         }
     }
 }
@@ -215,19 +221,26 @@ __device__ __forceinline__ T collide3(const Sweep3<T>& a, T f[kQ], T phi_prev, T
     return phi;
 }
 
-// Node coordinates of tile t (64 x 4 nodes of one z-slice) for the calling thread.
+// Node of the calling thread in tile t: kBlock consecutive lanes of a plane, a row taking a.row of them.
+// That is nx rounded up to whole 128-byte lines: narrow rows still fill the wavefronts (74 wide in FP32:
+// 96 lanes, 128 with a wavefront per row piece), and no line of the output is shared by two wavefronts
+// (rows packed end to end: 125^3 169 us a step in FP64 against 136, 230 x 110 x 200 309 in FP32 against
+// 205, from partial lines written to memory; 74 x 58 x 46 12.8 and 12.5).
 template <typename T>
 __device__ __forceinline__ bool node_of(const Sweep3<T>& a, int t, int& x, int& y, int& z)
 {
-    const int per_slice = a.tiles_x * a.tiles_y;
-    z = t / per_slice;
-    const int r = t - z * per_slice;
-    const int ty = r / a.tiles_x, tx = r - ty * a.tiles_x;
-    x = tx * kTileX + static_cast<int>(threadIdx.x % kTileX);
-    y = ty * kTileY + static_cast<int>(threadIdx.x / kTileX);
+    z = t / a.tiles_x;
+    const int k = (t - z * a.tiles_x) * kBlock + static_cast<int>(threadIdx.x);
+    y = k / a.row;
+    x = k - y * a.row;
     return x < a.nx && y < a.ny;
 }
 
+// One step. Below some 10^5 nodes the latency of a workgroup's one pass bounds it, above the bytes (328 a
+// node and step in FP64, 5.0 TB/s at 100 x 90 x 80). us a step with six Dirichlet faces and a source, before
+// (64 x 4 tiles; the nodes at faces on a path of their own, after the interior ones of their wavefront) and
+// after: 20^3 FP64 9.4 and 5.4, 74 x 58 x 46 20.6 and 12.6, FP32 13.5 and 8.0, 125^3 149 and 139; periodic
+// 125^3 138 and 136.
 template <typename T, bool SRC, bool KPHI, bool NT>
 __global__ __launch_bounds__(kBlock) void sweep3_kernel(Sweep3<T> a)
 {
@@ -737,9 +750,10 @@ template <typename T>
 hipError_t launch3_sweep(const Sweep3<T>& in, bool src, bool k1_per_node, hipStream_t s)
 {
     Sweep3<T> a = in;
-    a.tiles_x = (a.nx + kTileX - 1) / kTileX;
-    a.tiles_y = (a.ny + kTileY - 1) / kTileY;
-    const int64_t tiles = static_cast<int64_t>(a.tiles_x) * a.tiles_y * a.nz;
+    constexpr int line = 128 / static_cast<int>(sizeof(T));
+    a.row = (a.nx + line - 1) / line * line;
+    a.tiles_x = static_cast<int>((static_cast<int64_t>(a.row) * a.ny + kBlock - 1) / kBlock);  // per plane
+    const int64_t tiles = static_cast<int64_t>(a.tiles_x) * a.nz;
     if (tiles > INT32_MAX) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(tiles)), block(kBlock);
     return a.nts ? launch3_one<T, true>(a, src, k1_per_node, grid, block, s)
