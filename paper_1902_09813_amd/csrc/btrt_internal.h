@@ -121,7 +121,8 @@ struct LaunchCfg {
     // Set by resolve_launch for automatic shapes; not part of the public shape.
     int fuse = 0;       // time steps the launches take where they differ from `steps` (0: steps)
     int fit_rows = 0;   // moment walkers: rows per strip fitted to the resident wavefront slots (0: rows)
-    int block = 0;      // small grids: threads per workgroup of the block kernels (0: none)
+    int block = 0;      // threads per workgroup of the block kernels (0: none)
+    int wrows = 0;      // moment form, block > 0: rows per wavefront of the region kernel (0: one node per thread)
 };
 constexpr int kWalkGroup = 4;
 

@@ -665,6 +665,14 @@ hipError_t mom_block_launch(SweepArgs<T> a, int steps, int threads, int log_ex, 
     return hipGetLastError();
 }
 
+}  // namespace
+}  // namespace btrtk
+
+#include "btrt_mom_tile.h"
+
+namespace btrtk {
+namespace {
+
 // ---- many instances in one launch (see the population form's batched kernels) ---------------
 template <typename T>
 __global__ __launch_bounds__(kBlock) void mom_batch1_kernel(const BatchEntry<T>* __restrict__ ent,
@@ -803,6 +811,11 @@ int mom_fit_rows(const SweepArgs<T>& a)
 // a launch costs more than the redundant rows of a short walk.
 constexpr int kMomSmall = 4;
 
+// Nodes up to which automatic shapes take the block kernel (one node per thread) instead of regions.
+// (FP64 and FP32 hill, us a step: 300^2 blocks 1.15 and 0.95, regions 1.3 and 1.0; 362^2 blocks 1.54 and
+// 1.27, regions of 400 x 370 1.30 and 0.99.)
+constexpr int64_t kMomBlockNodes = 100000;
+
 template <typename T, bool SRC, int KM>
 int mom_fit(const SweepArgs<T>& a, int steps)
 {
@@ -853,6 +866,23 @@ LaunchCfg mom_resolve(const SweepArgs<T>& a, LaunchCfg cfg)
                 cfg.block = b.threads;
             }
         }
+        // Above, the region kernel; FP64 only up to 2^20 nodes (2^21 periodic without an A0 field), above which
+        // both kernels run at what the card's power allows and the walkers issue less. us a step, walkers and
+        // regions: FP32 hill 500^2 1.83 and 1.14, 1024^2 3.22 and 2.42, 2600 x 2200 11.9 and 10.5; with walls
+        // and a source 500^2 3.20 and 1.47, 1700 x 900 5.4 and 4.9; FP64 hill 500^2 2.04 and 1.50, 1024^2 4.5
+        // and 4.0, 1700 x 900 5.9 and 5.4, 2000^2 13.6 and 14.5; walls 500^2 3.9 and 2.3, 850 x 1200 6.0 and
+        // 5.4, 1700 x 900 7.5 and 8.2; A0 field 500^2 3.4 and 2.1, 1300^2 10.4 and 10.9.
+        if constexpr (!GEN) {
+            const int64_t most = fp64 ? (periodic && (KM & kK1Mask) != kK1Field ? (1LL << 21) : (1LL << 20) - 1) : nodes;
+            if (nodes > kMomBlockNodes && nodes <= most) {
+                const RegionShape r = mom_region_shape<T, SRC, KM>(a);
+                if (r.steps > 0) {
+                    cfg.fuse = r.steps;
+                    cfg.block = kWave * r.waves;
+                    cfg.wrows = r.rows;
+                }
+            }
+        }
     }
     if (cfg.steps != 2) cfg.tile = 0;
     if (cfg.steps == 1) {
@@ -890,6 +920,17 @@ template <typename T, bool SRC, int KM>
 hipError_t mom_variant(const SweepArgs<T>& a, const LaunchCfg& cfg, hipStream_t s)
 {
     if (cfg.steps < 1 || cfg.steps > kMaxFuse) return hipErrorInvalidValue;
+    if constexpr ((KM & kGen) == 0) {
+        if (cfg.wrows > 0 && cfg.steps > 1) {
+            const int waves = cfg.block / kWave;
+            switch (cfg.wrows) {
+                case 2: return mom_region_launch<T, SRC, KM, 2>(a, cfg.steps, waves, s);
+                case 4: return mom_region_launch<T, SRC, KM, 4>(a, cfg.steps, waves, s);
+                case 6: return mom_region_launch<T, SRC, KM, 6>(a, cfg.steps, waves, s);
+                default: return hipErrorInvalidValue;
+            }
+        }
+    }
     if (cfg.block > 0 && cfg.steps > 1)
         return mom_block_launch<T, SRC, KM>(a, cfg.steps, cfg.block, block_log_ex(cfg.block), s);
     int rows = cfg.fit_rows > 0 ? cfg.fit_rows : cfg.rows;
