@@ -380,8 +380,10 @@ typedef struct {
  * tiles; 4, 6 or 7 = k: strip walkers, one wavefront per strip of 66 - 2k columns by strip_rows
  * rows), resident blocks per compute unit of the persistent grid (0: one block per tile or
  * strip; with a walker four one-wavefront blocks per unit), launches captured per HIP graph replay (0: no graph;
- * otherwise even, >= 2), and the walkers' strip height (0: 16; at most 4096). Every
- * configuration gives the same bits. */
+ * otherwise even, >= 2), and the walkers' strip height (0: 16; at most 4096). With
+ * strip_rows 0 and two steps or more, instances with k0 = 1 and K2 = 1 advance on regions of 64 columns
+ * shared by a workgroup instead, whose height is chosen for the batch. Every configuration gives the
+ * same bits. */
 typedef struct {
     int32_t steps_per_launch;
     int32_t blocks_per_cu;
@@ -417,7 +419,7 @@ int btrt_batch_get_config(const btrt_batch_t* b, btrt_batch_config_t* cfg);
 /* Autotuner: times each candidate configuration on the batch itself by running steps of the
  * solve (every configuration computes the same bits, so these steps count as ordinary
  * steps), at most max_steps in total; keeps and reports the fastest per step. Candidates
- * (11): walkers of 4, 6 and 7 steps with 16- and 32-row strips and 16-launch graphs; 4-step
+ * (14): 4, 6 and 7 steps with strip_rows 0, 16 and 32 and 16-launch graphs; 4-step
  * walkers with 32-row strips without graphs and with 4 blocks per CU; 2 steps with and without
  * graphs; 1 step with graphs. After a warm-up of the configuration in force (at most
  * max_steps / 10 steps), each candidate takes k or 2 k untimed steps (k steps per launch; the

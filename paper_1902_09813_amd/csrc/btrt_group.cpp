@@ -34,10 +34,13 @@ int grid_blocks(const Group& g) { return g.cfg.blocks_per_cu > 0 ? g.ncu * g.cfg
 constexpr int kDefaultStripRows = 16;
 int strip_rows(const btrt_batch_config_t& c) { return c.strip_rows > 0 ? c.strip_rows : kDefaultStripRows; }
 
+// Members in the moment form advance on regions where no strip height is set (kRegions), else in strips.
+constexpr int kRegions = -1;
+
 // Rows of a unit of `steps` steps: the configured strip height, or the tiles' own below four steps.
 int unit_rows(const Group& g, int p, int steps)
 {
-    (void)p;
+    if (p == 1 && steps > 1 && g.cfg.strip_rows == 0) return kRegions;
     return btrtk::batch_walks(steps) ? strip_rows(g.cfg) : btrtk::tile_rows(steps, g.precision == BTRT_F64 ? 8 : 4);
 }
 
@@ -48,6 +51,14 @@ hipError_t part_launch(Group& g, int p, int slot, int steps, int flip)
     const int n = static_cast<int>(P.inst.size());
     const int rows = unit_rows(g, p, steps);
     if (n == 0 || P.total[slot] == 0) return hipSuccess;
+    if (p == 1 && rows == kRegions) {
+        if (g.precision == BTRT_F64)
+            return btrtk::launch_batch_region<double>(static_cast<const BatchEntry<double>*>(P.d_ent), P.d_begin[slot],
+                                                      P.d_par, n, P.total[slot], flip, steps, grid_blocks(g),
+                                                      P.region[steps], g.stream);
+        return btrtk::launch_batch_region<float>(static_cast<const BatchEntry<float>*>(P.d_ent), P.d_begin[slot], P.d_par,
+                                                 n, P.total[slot], flip, steps, grid_blocks(g), P.region[steps], g.stream);
+    }
     if (p == 1) {
         if (g.precision == BTRT_F64)
             return btrtk::launch_batch_mom<double>(static_cast<const BatchEntry<double>*>(P.d_ent), P.d_begin[slot], P.d_par,
@@ -71,6 +82,20 @@ hipError_t raw_launch(Group& g, int steps, int flip)
     return e == hipSuccess ? part_launch(g, 1, steps, steps, flip) : e;
 }
 
+btrtk::BatchGrid grid_of(const Instance& I)
+{
+    return btrtk::BatchGrid{I.nx, I.ny, I.perx != 0, I.pery != 0};
+}
+
+btrtk::BatchRegion region_shape(const Group& g, int steps)
+{
+    std::vector<btrtk::BatchGrid> grids;
+    for (const Instance* I : g.part[1].inst) grids.push_back(grid_of(*I));
+    const int n = static_cast<int>(grids.size());
+    return g.precision == BTRT_F64 ? btrtk::batch_region<double>(grids.data(), n, steps)
+                                   : btrtk::batch_region<float>(grids.data(), n, steps);
+}
+
 // Offsets of each member's units in part p's concatenated list for `steps` per launch: 64 x rows
 // tiles, or walker strips. skip_first: members whose first step is free get no units.
 int upload_begin(Group& g, int p, int slot, int steps, int rows, bool skip_first)
@@ -79,13 +104,16 @@ int upload_begin(Group& g, int p, int slot, int steps, int rows, bool skip_first
     const int n = static_cast<int>(P.inst.size());
     if (n == 0) return BTRT_OK;
     std::vector<int> begin(n + 1);
+    if (rows == kRegions) P.region[steps] = region_shape(g, steps);
     const int width = p == 1 ? btrtk::mom_strip_columns(steps)
                              : (btrtk::batch_walks(steps) ? btrtk::batch_strip_columns(steps) : btrtk::kTileWidth);
     int64_t acc = 0;
     for (int i = 0; i < n; ++i) {
         begin[i] = static_cast<int>(acc);
         const Instance& I = *P.inst[i];
-        if (!(skip_first && I.first_step_free()))
+        if (rows == kRegions)
+            acc += btrtk::batch_regions(grid_of(I), steps, P.region[steps].rows * P.region[steps].waves);
+        else if (!(skip_first && I.first_step_free()))
             acc += static_cast<int64_t>((I.nx + width - 1) / width) * ((I.ny + rows - 1) / rows);
     }
     if (acc > INT32_MAX) return fail(BTRT_E_INVAL, "more than 2^31 - 1 tiles in one group");
@@ -273,6 +301,30 @@ int first_step(Group& g)
 
 }  // namespace
 
+// Steps per launch by the members' states. All in the moment form: the regions' model picks. Else, with
+// few nodes, whose rounds are latency-bound, the fully parallel two-step tiles; from kAutoWalkNodes on
+// (measured with a served workload) four-step units, which move the state once per four steps.
+btrt_batch_config_t group_auto(const Group& g)
+{
+    constexpr int64_t kAutoWalkNodes = int64_t(1) << 21;
+    if (!g.part[0].inst.empty()) {
+        int64_t nodes = 0;
+        for (const Instance* I : g.inst) nodes += static_cast<int64_t>(I->nx) * I->ny;
+        return btrt_batch_config_t{nodes >= kAutoWalkNodes ? 4 : 2, 0, 0, 0};
+    }
+    btrt_batch_config_t best{2, 0, 0, 0};
+    double best_t = 0;
+    if (g.part[1].inst.empty()) return best;
+    for (int k : {2, 4, 6, 7}) {
+        const double t = region_shape(g, k).cost / k;
+        if (best_t == 0 || t < best_t) {
+            best_t = t;
+            best.steps_per_launch = k;
+        }
+    }
+    return best;
+}
+
 int group_enqueue(Group& g, int64_t n)
 {
     if (g.inst.empty()) return BTRT_OK;
@@ -298,7 +350,7 @@ int group_enqueue(Group& g, int64_t n)
             }
             if (!g.gexec || g.gcfg.steps_per_launch != g.cfg.steps_per_launch ||
                 g.gcfg.blocks_per_cu != g.cfg.blocks_per_cu || g.gcfg.graph_launches != L ||
-                strip_rows(g.gcfg) != strip_rows(g.cfg)) {
+                g.gcfg.strip_rows != g.cfg.strip_rows) {
                 int rc = build_graph(g);
                 if (rc != BTRT_OK) return rc;
             }
@@ -348,7 +400,7 @@ int group_tune(Group& g, int64_t max_steps, btrt_batch_config_t* best, int64_t* 
 {
     std::vector<btrt_batch_config_t> cand;
     for (int k : {4, 6, 7})
-        for (int rows : {16, 32}) cand.push_back({k, 0, 16, rows});
+        for (int rows : {0, 16, 32}) cand.push_back({k, 0, 16, rows});
     cand.push_back({4, 0, 0, 32});
     cand.push_back({4, 4, 16, 32});
     for (int gl : {0, 16}) cand.push_back({2, 0, gl, 0});

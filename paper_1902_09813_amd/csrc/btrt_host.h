@@ -5,6 +5,7 @@
 
 #include "btrt.h"
 #include "btrt_internal.h"
+#include "btrt_mom_batch.h"
 #include "btrt_transfer.h"
 
 #include <hip/hip_runtime.h>
@@ -175,7 +176,8 @@ struct Group {
         int* d_begin[btrtk::kBatchMaxSteps + 1] = {};  // indexed by steps per launch (1, 2, 4, 6, 7); 0: see below
         int* d_par = nullptr;
         int total[btrtk::kBatchMaxSteps + 1] = {};
-        int built_rows[btrtk::kBatchMaxSteps + 1] = {};  // strip height each table was built for (0: not built)
+        int built_rows[btrtk::kBatchMaxSteps + 1] = {};  // strip height each table was built for (0: not built, -1: regions)
+        btrtk::BatchRegion region[btrtk::kBatchMaxSteps + 1];  // shape of the tables of regions
     };
     Part part[2];
     int flip = 0;       // launches since group_upload, mod 2
@@ -191,6 +193,8 @@ struct Group {
 int group_init(Group& g, int device, hipStream_t s, int precision, int capacity);
 // Rebuilds the device tables from g.inst (synchronous); drops the captured graph.
 int group_upload(Group& g);
+// The launch configuration for the members as they are, none set (after group_upload).
+btrt_batch_config_t group_auto(const Group& g);
 // Enqueues n time steps of every member.
 int group_enqueue(Group& g, int64_t n);
 // Eq. (64) residual of every member into out[size]; *bad = members with NaN/Inf (out NaN).

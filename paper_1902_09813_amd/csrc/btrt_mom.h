@@ -674,6 +674,25 @@ namespace btrtk {
 namespace {
 
 // ---- many instances in one launch (see the population form's batched kernels) ---------------
+// Arguments of member i at parity p, both uniform: read through the constant address space, into scalar
+// registers as a single grid's kernel arguments are. (Plain loads in a loop that also stores come into
+// vector registers.)
+template <typename T>
+__device__ __forceinline__ SweepArgs<T> entry_args(const BatchEntry<T>* ent, int i, int p)
+{
+    constexpr int kWords = sizeof(SweepArgs<T>) / sizeof(unsigned);
+    static_assert(kWords * sizeof(unsigned) == sizeof(SweepArgs<T>), "whole words");
+    struct Words {
+        unsigned w[kWords];
+    };
+    using Const = const __attribute__((address_space(4))) unsigned;
+    Const* src = (Const*)(&ent[__builtin_amdgcn_readfirstlane(i)].a[__builtin_amdgcn_readfirstlane(p)]);
+    Words v;
+#pragma unroll
+    for (int k = 0; k < kWords; ++k) v.w[k] = src[k];
+    return __builtin_bit_cast(SweepArgs<T>, v);
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void mom_batch1_kernel(const BatchEntry<T>* __restrict__ ent,
                                                             const int* __restrict__ begin, const int* __restrict__ par,
@@ -682,7 +701,7 @@ __global__ __launch_bounds__(kBlock) void mom_batch1_kernel(const BatchEntry<T>*
     const int g = static_cast<int>(gridDim.x);
     for (int t = xcd_tile(); t < total; t += g) {
         const int i = owner(begin, ninst, t);
-        const SweepArgs<T> a = ent[i].a[par[i] ^ flip];
+        const SweepArgs<T> a = entry_args(ent, i, par[i] ^ flip);
         const int local = t - begin[i];
         const int tiles_x = (a.nx + kTileX - 1) / kTileX;
         const int ty = local / tiles_x, tx = local - ty * tiles_x;
@@ -704,7 +723,7 @@ __global__ __launch_bounds__(kWave) void mom_batchw_kernel(const BatchEntry<T>* 
     const int lane = static_cast<int>(threadIdx.x);
     for (int t = xcd_tile(); t < total; t += g) {
         const int i = owner(begin, ninst, t);
-        SweepArgs<T> a = ent[i].a[par[i] ^ flip];
+        SweepArgs<T> a = entry_args(ent, i, par[i] ^ flip);
         a.tiles_x = (a.nx + MomWalk<K, 1>::W - 1) / MomWalk<K, 1>::W;
         const int local = t - begin[i];
         const int sy = local / a.tiles_x, sx = local - sy * a.tiles_x;

@@ -71,8 +71,9 @@ __host__ __device__ __forceinline__ RegionSpan region_span(int t, int n, int siz
 // costs up to half of what they compute (1531 x 977, four steps: 14 rows of 22), and a region of six rows
 // a lane by 12 wavefronts keeps 0.68 (six steps). The four parts of each row's sums are independent, so a
 // wavefront also has more to issue than a walker's chain of levels.
-template <typename T, bool SRC, int KM, int R, bool EDGE>
-__device__ __forceinline__ void mom_region(const SweepArgs<T>& a, const RegionSpan& X, const RegionSpan& Y, int steps, T* lds)
+// sfac: the source's factor of each step (a.sfac, or where its memory is).
+template <typename T, bool SRC, int KM, int R, bool EDGE, typename F>
+__device__ __forceinline__ void mom_region(const SweepArgs<T>& a, F sfac, const RegionSpan& X, const RegionSpan& Y, int steps, T* lds)
 {
     constexpr int SRCG = mom_srcg<SRC, KM>();
     const int lane = static_cast<int>(threadIdx.x % kWave);
@@ -143,7 +144,7 @@ __device__ __forceinline__ void mom_region(const SweepArgs<T>& a, const RegionSp
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
                         wall[i] = a.wall[i];
-                        asm volatile("" : "+s"(wall[i]));  // formed here, not held in registers through the launch
+                        asm volatile("" : "+v"(wall[i]));  // formed here, not held in registers through the launch
                     }
                     mom_walls(node(j), oxm, oxp, oym, oyp,
                               [&](int i, bool ox, bool oy) { return side_wall(wall, i, ox, oy); }, f);
@@ -165,7 +166,7 @@ __device__ __forceinline__ void mom_region(const SweepArgs<T>& a, const RegionSp
             }
             Ap = cur.Ap;
             Cp = cur.Cp;
-            v[j] = mom_collide<T, SRC, KM>(a, f, v[j].phi, SRC ? src[SRC ? j : 0] * a.sfac[s] : T(0), row(j) * a.pitch + x);
+            v[j] = mom_collide<T, SRC, KM>(a, f, v[j].phi, SRC ? src[SRC ? j : 0] * sfac[s] : T(0), row(j) * a.pitch + x);
             cur = next;
         }
     }
@@ -175,19 +176,19 @@ __device__ __forceinline__ void mom_region(const SweepArgs<T>& a, const RegionSp
         if (out && cy + j >= Y.lo && cy + j < Y.hi) mom_put<T, SRC, KM>(a, (cy + j) * a.pitch + cx, v[j]);
 }
 
-template <typename T, bool SRC, int KM, int R, bool WALLS>
-__device__ __forceinline__ void mom_region_any(const SweepArgs<T>& a, int tx, int ty, int steps, T* lds)
+template <typename T, bool SRC, int KM, int R, bool WALLS, typename F>
+__device__ __forceinline__ void mom_region_any(const SweepArgs<T>& a, F sfac, int tx, int ty, int steps, T* lds)
 {
     const RegionSpan X = region_span(tx, a.nx, kWave, steps, !WALLS || a.perx);
     const RegionSpan Y = region_span(ty, a.ny, static_cast<int>(blockDim.x) / kWave * R, steps, !WALLS || a.pery);
     // (The choice is uniform over the workgroup: every wavefront meets the same barriers.)
     if constexpr (WALLS) {
         if (X.wall || Y.wall) {
-            mom_region<T, SRC, KM, R, true>(a, X, Y, steps, lds);
+            mom_region<T, SRC, KM, R, true>(a, sfac, X, Y, steps, lds);
             return;
         }
     }
-    mom_region<T, SRC, KM, R, false>(a, X, Y, steps, lds);
+    mom_region<T, SRC, KM, R, false>(a, sfac, X, Y, steps, lds);
 }
 
 constexpr int kRegionWaves = 16;  // most wavefronts of a region: 128 registers a lane, which six rows fit
@@ -198,7 +199,7 @@ __global__ __launch_bounds__(kWave* kRegionWaves) void mom_region_kernel(SweepAr
     extern __shared__ __attribute__((aligned(16))) char region_lds[];
     const int tile = xcd_tile();
     const int ty = tile / a.tiles_x;
-    mom_region_any<T, SRC, KM, R, WALLS>(a, tile - ty * a.tiles_x, ty, steps, reinterpret_cast<T*>(region_lds));
+    mom_region_any<T, SRC, KM, R, WALLS>(a, static_cast<const T*>(a.sfac), tile - ty * a.tiles_x, ty, steps, reinterpret_cast<T*>(region_lds));
 }
 
 template <typename T>

@@ -97,9 +97,6 @@ struct Request {
 
 }  // namespace
 
-// Resident nodes from which an automatic launch configuration uses the strip walkers (measured
-// on gfx950 with the served workload: below it the rounds are latency-bound).
-constexpr int64_t kAutoWalkNodes = int64_t(1) << 21;
 // With the automatic launch configuration, a request of at least this many nodes fills the GPU by
 // itself: it advances by its own launches in the automatic single-grid shape (the seven-step
 // walker on large periodic grids) instead of sharing the batched launch of the smaller requests,
@@ -328,14 +325,7 @@ int btrt_server_pump(btrt_server_t* s, int32_t* active, int32_t* queued)
         s->dirty = false;
     }
     if (rc == BTRT_OK && !s->active.empty()) {
-        if (s->auto_launch) {
-            // Few resident nodes: the rounds are latency-bound and the fully parallel two-step
-            // tiles finish them sooner; from kAutoWalkNodes on, four-step strip walkers (16-row
-            // strips) move the state once per four steps. Every configuration gives the same bits.
-            int64_t nodes = 0;
-            for (const Instance* I : s->group.inst) nodes += static_cast<int64_t>(I->nx) * I->ny;
-            s->group.cfg = nodes >= kAutoWalkNodes ? btrt_batch_config_t{4, 0, 0, 16} : btrt_batch_config_t{2, 0, 0, 0};
-        }
+        if (s->auto_launch) s->group.cfg = group_auto(s->group);  // every configuration gives the same bits
         rc = group_enqueue(s->group, s->check_interval);
         for (int64_t id : s->active) {
             Instance& I = s->req[id]->inst;
