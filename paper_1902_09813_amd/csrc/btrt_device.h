@@ -396,9 +396,13 @@ __global__ __launch_bounds__(1024) void block_kernel(SweepArgs<typename F::T> a,
         phi = a.phi_prev[n];
     }
     const T tw1 = T(2) * Lat<T>::w1, tw5 = T(2) * Lat<T>::w5;
+    NodePowers<T> pows{T(0), T(0)};
+    if constexpr (GEN)
+        if (node) pows = node_powers(a, phi);
     for (int s = 0; s < steps; ++s) {
         if (node) {
-            const T now = collide<T, SRC, collide_mode<F, KM>()>(a, f, phi, source_at<T, SRC>(a, n, x, y, s), n);
+            const T now = collide<T, SRC, collide_mode<F, KM>()>(a, f, phi, source_at<T, SRC>(a, n, x, y, s), n,
+                                                                 GEN ? &pows : nullptr);
             if (s == steps - 1) {
                 if (out) F::template put<false>(a, n, f, now);
             } else {

@@ -21,7 +21,8 @@
 // What bounds it: on large grids the issue of FP64/FP32 instructions (63 VALU instructions per FP64
 // update and lane at seven steps, 114 in the population walker; three words of state move per node
 // and launch instead of ten). Measured per step, population form -> moment form: 4096^2 nonlinear
-// FP64 92 -> 48 us, FP32 57 -> 30 us; 1024^2 with walls FP64 14.6 -> 6.3 us; 64^2 FP64 4.1 -> 1.3 us.
+// FP64 92 -> 47 us, FP32 57 -> 27 us (regions); 1024^2 with walls FP64 14.6 -> 5.7 us; 64^2 FP64 4.1 -> 0.73
+// us (blocks).
 //
 // State after n >= 1 steps: f+(n-1) as (phi(n-1), q(n-1), g(n-1)). At n = 0 the planes already
 // hold f+(0) (f(0) = f^eq(phi0), so phi(0) = phi0 and q(0) = B(phi0) pointwise): the first step
@@ -146,7 +147,8 @@ struct MomState {
 // The collision on the pulled moments: collide() of the population form with k0 = 1 and Q = 0. s is
 // the part of the source that does not depend on phi.
 template <typename T, bool SRC, int KM>
-__host__ __device__ __forceinline__ MomState<T> mom_collide(const SweepArgs<T>& a, const MomPart<T>& f, T phi_prev, T s, int n)
+__host__ __device__ __forceinline__ MomState<T> mom_collide(const SweepArgs<T>& a, const MomPart<T>& f, T phi_prev, T s, int n,
+                                                             NodePowers<T>* pows = nullptr)
 {
     constexpr int K1M = KM & kK1Mask;
     constexpr bool GEN = (KM & kGen) != 0;
@@ -157,7 +159,8 @@ __host__ __device__ __forceinline__ MomState<T> mom_collide(const SweepArgs<T>& 
     T By = phi * fmadd(hby, phi, a.ay);
     T dBx, dBy;
     if (GEN && (a.fcx != T(0) || a.fcy != T(0))) {
-        const T pw = abspow(phi, a.fq), pwp = abspow(phi_prev, a.fq);
+        const T pw = abspow(phi, a.fq), pwp = pows ? pows->flux : abspow(phi_prev, a.fq);
+        if (pows) pows->flux = pw;
         const T Bxp = fmadd(a.fcx, pwp, phi_prev * fmadd(hbx, phi_prev, a.ax));
         const T Byp = fmadd(a.fcy, pwp, phi_prev * fmadd(hby, phi_prev, a.ay));
         Bx = fmadd(a.fcx, pw, Bx);
@@ -169,8 +172,10 @@ __host__ __device__ __forceinline__ MomState<T> mom_collide(const SweepArgs<T>& 
         dBy = fmadd(-phi_prev, fmadd(hby, phi_prev, a.ay), By);
     }
     if (GEN && a.rr != T(0)) {
-        const T R = (a.rr * phi) * (T(1) - abspow(phi, a.rp));
-        const T Rp = (a.rr * phi_prev) * (T(1) - abspow(phi_prev, a.rp));
+        const T pr = abspow(phi, a.rp), prp = pows ? pows->source : abspow(phi_prev, a.rp);
+        if (pows) pows->source = pr;
+        const T R = (a.rr * phi) * (T(1) - pr);
+        const T Rp = (a.rr * phi_prev) * (T(1) - prp);
         s = s + fmadd(T(1.5), R, -half * Rp);
     }
     const T hx = fmadd(half, dBx, jx - Bx), hy = fmadd(half, dBy, jy - By);
@@ -628,6 +633,8 @@ __global__ __launch_bounds__(1024) void mom_block_kernel(SweepArgs<T> a, int ste
         v.g = SRCG == 1 || (SRCG == 2 && a.mom_g) ? a.fin[kMomG * a.plane + n] : v.phi;
         if constexpr (SRC) src = mom_source(a, n, x, y);
     }
+    NodePowers<T> pows{T(0), T(0)};
+    if constexpr (GEN) pows = node_powers(a, v.phi);
     for (int s = 0; s < steps; ++s) {
         MomNode<T> N = mom_node(v.g, v.qx, v.qy);
         if (!node) N = MomNode<T>{};
@@ -647,7 +654,7 @@ __global__ __launch_bounds__(1024) void mom_block_kernel(SweepArgs<T> a, int ste
         if (edge)
             mom_walls(N, oxm, oxp, oym, oyp,
                       [&](int i, bool ox, bool oy) { return mom_wall<T, GEN>(a, x, y, s, i, ox, oy); }, f);
-        v = mom_collide<T, SRC, KM>(a, f, v.phi, SRC ? src * a.sfac[s] : T(0), n);
+        v = mom_collide<T, SRC, KM>(a, f, v.phi, SRC ? src * a.sfac[s] : T(0), n, GEN ? &pows : nullptr);
     }
     if (out) mom_put<T, SRC, KM>(a, n, v);
 }

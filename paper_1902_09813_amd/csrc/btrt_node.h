@@ -195,6 +195,19 @@ __host__ __device__ inline T sum9(const T f[9])
     return (f[0] + (f[1] + f[3])) + ((f[2] + f[4]) + ((f[5] + f[7]) + (f[6] + f[8])));
 }
 
+// Powers of the general model at a node's phi(t-1), kept from the step before by kernels that take several
+// (four powers a step are most of its time; two are the last step's).
+template <typename T>
+struct NodePowers {
+    T flux, source;  // |phi|^fq, |phi|^rp (0 where the model has no such term)
+};
+
+template <typename T>
+__host__ __device__ inline NodePowers<T> node_powers(const SweepArgs<T>& a, T phi)
+{
+    return NodePowers<T>{a.fcx != T(0) || a.fcy != T(0) ? abspow(phi, a.fq) : T(0), a.rr != T(0) ? abspow(phi, a.rp) : T(0)};
+}
+
 // One node of the B-TriRT collision; f holds f(x, t) on entry and f+(x, t) on return. Returns
 // phi(t). Eq. (6) with f^neq = f - f^eq is used in the form
 //     f_i+ = (1 - k0) f_i + w_i [E_i + 3 c_i . q],
@@ -210,7 +223,7 @@ __host__ __device__ inline T sum9(const T f[9])
 // in-plane index (read only for an A0 field). s is the part of the source term of the step that
 // does not depend on phi, with the Scheme 2 correction folded in.
 template <typename T, int SRC, int KM>
-__host__ __device__ inline T collide(const SweepArgs<T>& a, T f[9], T phi_prev, T s, int n)
+__host__ __device__ inline T collide(const SweepArgs<T>& a, T f[9], T phi_prev, T s, int n, NodePowers<T>* pows = nullptr)
 {
     constexpr int K1M = KM & kK1Mask;
     constexpr bool GEN = (KM & kGen) != 0;
@@ -237,7 +250,8 @@ __host__ __device__ inline T collide(const SweepArgs<T>& a, T f[9], T phi_prev, 
     T dBx, dBy;
     if (GEN && (a.fcx != T(0) || a.fcy != T(0))) {
         // General model: B gains c |phi|^q.
-        const T pw = abspow(phi, a.fq), pwp = abspow(phi_prev, a.fq);
+        const T pw = abspow(phi, a.fq), pwp = pows ? pows->flux : abspow(phi_prev, a.fq);
+        if (pows) pows->flux = pw;
         const T Bxp = fmadd(a.fcx, pwp, phi_prev * fmadd(hbx, phi_prev, a.ax));
         const T Byp = fmadd(a.fcy, pwp, phi_prev * fmadd(hby, phi_prev, a.ay));
         Bx = fmadd(a.fcx, pw, Bx);
@@ -251,8 +265,10 @@ __host__ __device__ inline T collide(const SweepArgs<T>& a, T f[9], T phi_prev, 
     if (GEN && a.rr != T(0)) {
         // General model: S(phi) = r phi (1 - |phi|^p) with the Scheme 2 correction,
         // S(t) + (S(t) - S(t-1))/2, S(t-1) taken at phi(t-1).
-        const T R = (a.rr * phi) * (T(1) - abspow(phi, a.rp));
-        const T Rp = (a.rr * phi_prev) * (T(1) - abspow(phi_prev, a.rp));
+        const T pr = abspow(phi, a.rp), prp = pows ? pows->source : abspow(phi_prev, a.rp);
+        if (pows) pows->source = pr;
+        const T R = (a.rr * phi) * (T(1) - pr);
+        const T Rp = (a.rr * phi_prev) * (T(1) - prp);
         s = s + fmadd(T(1.5), R, -half * Rp);
     }
 
