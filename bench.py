@@ -31,16 +31,17 @@ FP64_PEAK_TFLOPS = 78.6
 # instruction of a 64-wide wavefront occupies its SIMD for four cycles, and so does every FP32 or
 # 16-bit one that is not packed).
 FP64_ISSUE_PEAK_T = 39.3
-# One node update of the 4096^2 nonlinear workload (k0 = 1, K1 per node, Burgers flux, no source)
-# as the collision is written: FP64 flops (an FMA counts two) and FP64 VALU instructions.
-FLOPS_PER_UPDATE = 112
-FP64_INSTRUCTIONS_PER_UPDATE = 81
+# One node update of the 4096^2 nonlinear workload (k0 = K2 = 1, K1 per node, Burgers flux, no source)
+# as the moment form's pull and collision are written: FP64 flops (an FMA counts two) and FP64 VALU
+# instructions.
+FLOPS_PER_UPDATE = 77
+FP64_INSTRUCTIONS_PER_UPDATE = 50
 BYTES_PER_UPDATE_F64 = 160  # 9 populations + phi read, the same written, per node update
 CHECK_INTERVAL = 1000
 METRIC = "MLUPS and % HBM roofline, batched/served vs plain; p50/p99 solve latency"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_traffic.json")
 CSRC = os.path.join(ROOT, "paper_1902_09813_amd", "csrc")
-KERNEL_SOURCES = ("btrt_internal.h", "btrt_node.h", "btrt_device.h", "btrt_sweep_f64.hip", "btrt_sweep_f32.hip",
+KERNEL_SOURCES = ("btrt_mom.h", "btrt_mom_tile.h", "btrt_mom_f64.hip", "btrt_mom_f32.hip", "btrt_internal.h", "btrt_node.h", "btrt_device.h", "btrt_sweep_f64.hip", "btrt_sweep_f32.hip",
                   "btrt_sweep_k0_f64.hip", "btrt_sweep_k0_f32.hip", "btrt_sweep_k0_f16dev.hip",
                   "btrt_sweep_k0_bf16dev.hip", "btrt_sweep_f16dev.hip", "btrt_sweep_bf16dev.hip",
                   "btrt_batch_kernels.hip", "btrt_kernels.hip")
@@ -64,6 +65,14 @@ def sweep_launches(steps, fusion):
         n += k // fusion + (1 if k % fusion else 0)
         done += k
     return n
+
+
+def state_bytes(w, info):
+    """Bytes a launch reads and writes per node: with k0 = K2 = 1 the state is phi and the first moments
+    (and g with a source) in the format computed in, FP64 or FP32, else what the library reports."""
+    if w.k0 != 1.0 or w.k2 != 1.0:
+        return info.bytes_per_node_launch
+    return 2.0 * (4 if w.source is not None else 3) * (8 if info.bytes_per_node_launch == 160 else 4)
 
 
 def timed_run(w, precision, steps, warmup, fusion=0, launch=None):
@@ -126,7 +135,7 @@ def timed_run(w, precision, steps, warmup, fusion=0, launch=None):
         "launches": sweep_launches(steps, fusion),
         "launch_ms_avg": sweep_ms / sweep_launches(steps, fusion),
         "mlups": nodes * steps / (total_ms * 1e-3) / 1e6,
-        "bytes_per_node_launch": info.bytes_per_node_launch,
+        "bytes_per_node_launch": state_bytes(w, info),
         "nodes": nodes,
         "residual": residual,
         "launch": {"steps_per_launch": shape[0], "strip_rows": shape[1], "strips_per_group": shape[2],
@@ -164,10 +173,11 @@ def timed_run3(w, precision, steps, warmup, launch=None):
     k = shape[0]
     launches = steps // k + steps % k
     launch_ms = ms / launches
-    bw = info.bytes_per_node_launch * nodes / (launch_ms * 1e-3) / 1e9
+    state = info.bytes_per_node_launch * 8 / 40  # k0 = K2 = 1: phi and three moments in and out, not 20 words
+    bw = state * nodes / (launch_ms * 1e-3) / 1e9
     return {"mlups": round(nodes * steps / (ms * 1e-3) / 1e6, 1), "launch_us": round(launch_ms * 1e3, 2),
             "launch": {"steps_per_launch": shape[0], "z_chunk": shape[1], "tile": shape[2]},
-            "bytes_per_node_launch": info.bytes_per_node_launch, "achieved_gbs": round(bw, 1),
+            "bytes_per_node_launch": state, "achieved_gbs": round(bw, 1),
             "hbm_frac": round(bw / HBM_PEAK_GBS, 4), "steps": steps}
 
 
