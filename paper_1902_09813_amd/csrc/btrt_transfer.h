@@ -7,7 +7,8 @@
 
 namespace btrth {
 
-// Copies behind the work already on s and returns when complete. `device` is the current device.
+// Copies behind the work already on s and returns when complete. `device` is the current device; s may be
+// any stream, hipStreamPerThread among them.
 hipError_t copy_to_host(void* dst, const void* src, size_t bytes, int device, hipStream_t s);
 
 // A pinned buffer and its size, or null where none is to be had (the caller then stages through memory of

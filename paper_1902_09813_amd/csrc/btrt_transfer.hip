@@ -147,7 +147,10 @@ hipError_t copy_to_host(void* dst, const void* src, size_t bytes, int device, hi
     // Words the kernel could not move are left to the runtime's own path (64^2 FP64, the whole read: 33 us
     // by that, 19 by the kernel; 500^2 126 and 90 us).
     const bool words = bytes % 8 == 0 && reinterpret_cast<uintptr_t>(dev) % 16 == 0;
-    const int most = static_cast<int>(std::max<size_t>(1, std::min<size_t>(kThreads, bytes / kPerThread)));
+    // hipStreamPerThread names another stream in each thread, where nothing would order a share behind the
+    // work on the caller's: those reads stay on the calling thread.
+    const size_t threads = s == hipStreamPerThread ? 1 : kThreads;
+    const int most = static_cast<int>(std::max<size_t>(1, std::min<size_t>(threads, bytes / kPerThread)));
     char* pinned[kThreads];
     int want = 0;
     size_t got = 0;
