@@ -610,7 +610,12 @@ __device__ __forceinline__ T mom3_population(const Gather3<T>& g, int x, int y, 
         return wv<T>(i) * fmadd(sign * T(3), cq, gp[n]);
     };
     const int n = z * a.slab + y * a.pitch + x;
-    if (g.fresh) return post(n, a.phi_prev, T(1));
+    if (g.fresh) {  // FP64 arithmetic, rounded once
+        const double cq = cxv(i) * static_cast<double>(a.fin[kM3Qx * a.plane + n]) +
+                          cyv(i) * static_cast<double>(a.fin[kM3Qy * a.plane + n]) +
+                          czv(i) * static_cast<double>(a.fin[kM3Qz * a.plane + n]);
+        return static_cast<T>(wv<double>(i) * (static_cast<double>(a.phi_prev[n]) + 3.0 * cq));
+    }
     const T* gp = a.src ? a.fin + kM3G * a.plane : a.phi_prev;
     int s[3] = {x - cxv(i), y - cyv(i), z - czv(i)};
     const int dim[3] = {a.nx, a.ny, a.nz};

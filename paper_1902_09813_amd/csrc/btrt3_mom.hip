@@ -234,6 +234,7 @@ __global__ __launch_bounds__(kWave* NW) void mom3_kernel(Sweep3<T> a)
 // ---- reads and set-up ---------------------------------------------------------------------------
 constexpr int kBlock = 256;
 
+// f+(0) pointwise from phi0, in FP64 and rounded once, as in init3_kernel.
 template <typename T>
 __global__ __launch_bounds__(kBlock) void mom3_init_kernel(Sweep3<T> a, const double* __restrict__ phi0)
 {
@@ -241,11 +242,12 @@ __global__ __launch_bounds__(kBlock) void mom3_init_kernel(Sweep3<T> a, const do
     if (k >= static_cast<int64_t>(a.nx) * a.ny * a.nz) return;
     const int64_t row = k / a.nx;
     const int64_t n = row * a.pitch + (k - row * a.nx);
-    const T phi = static_cast<T>(phi0[k]);
-    a.phi_out[n] = phi;
+    const double p = phi0[k];
+    a.phi_out[n] = static_cast<T>(p);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) a.fout[c * a.plane + n] = phi * fma3(T(0.5) * a.b[c], phi, a.a[c]);
-    if (a.src) a.fout[kM3G * a.plane + n] = phi + a.src[n];
+    for (int c = 0; c < 3; ++c)
+        a.fout[c * a.plane + n] = static_cast<T>(p * (static_cast<double>(a.a[c]) + 0.5 * static_cast<double>(a.b[c]) * p));
+    if (a.src) a.fout[kM3G * a.plane + n] = static_cast<T>(p + static_cast<double>(a.src[n]));
 }
 
 template <typename T, bool SRC, bool KPHI, bool WALLS, int K, int NW, int R>

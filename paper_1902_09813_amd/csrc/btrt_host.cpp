@@ -472,8 +472,8 @@ int instance_setup(Instance& I, const btrt_grid_t* grid, const btrt_flux_t* B, c
     const double ab[4] = {B->a[0], B->a[1], B->b[0], B->b[1]};
     const double cq[3] = {B->c[0], B->c[1], B->c[0] != 0.0 || B->c[1] != 0.0 ? B->q : 1.0};
     if (I.mom)
-        err = I.precision == BTRT_F64 ? launch_mom_init<double>(sweep_args<double>(I, 1), I.kind, tmp, s)
-                                      : launch_mom_init<float>(sweep_args<float>(I, 1), I.kind, tmp, s);
+        err = I.precision == BTRT_F64 ? launch_mom_init<double>(sweep_args<double>(I, 1), I.kind, tmp, ab, cq, s)
+                                      : launch_mom_init<float>(sweep_args<float>(I, 1), I.kind, tmp, ab, cq, s);
     else if (I.precision == BTRT_F64)
         err = launch_init<double>(sweep_args<double>(I, 1), kFmtPlain, tmp, I.wall, ab, cq, r.dq, s);
     else

@@ -166,9 +166,11 @@ template <typename T>
 hipError_t launch_batch_mom(const BatchEntry<T>* ent, const int* begin, const int* par, int ninst, int total, int flip,
                             int steps, int grid, int rows, hipStream_t s);
 int mom_strip_columns(int steps);
-// f+(0) of the moment form into both buffers of a handle (a: the arguments of parity 1).
+// f+(0) of the moment form into both buffers of a handle (a: the arguments of parity 1; ab and cq as for
+// launch_init).
 template <typename T>
-hipError_t launch_mom_init(const SweepArgs<T>& a, int kind, const double* phi0, hipStream_t s);
+hipError_t launch_mom_init(const SweepArgs<T>& a, int kind, const double* phi0, const double ab[4], const double cq[3],
+                           hipStream_t s);
 // Tile height of the kernel that fuses `steps` steps (tile width is 64).
 int tile_rows(int steps, int precision_bytes);
 constexpr int kTileWidth = 64;

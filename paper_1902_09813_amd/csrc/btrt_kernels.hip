@@ -56,31 +56,29 @@ __device__ __forceinline__ void pull_any(const SweepArgs<typename F::T>& a, int 
 }
 
 // f+(0) of the moment form, pointwise from phi0 (q = B(phi0), g = phi0 + S(0)), into both buffers, so
-// that a launch of a batch may pass over an instance without a step of its own.
+// that a launch of a batch may pass over an instance without a step of its own. FP64 arithmetic, rounded
+// once, as in init_kernel.
 template <typename T>
-__global__ __launch_bounds__(kBlock) void mom_init_kernel(SweepArgs<T> a, int kind, const double* __restrict__ phi0)
+__global__ __launch_bounds__(kBlock) void mom_init_kernel(SweepArgs<T> a, int kind, const double* __restrict__ phi0,
+                                                          InitConsts c)
 {
     const int64_t k = static_cast<int64_t>(blockIdx.x) * kBlock + threadIdx.x;
     if (k >= static_cast<int64_t>(a.nx) * a.ny) return;
     const int y = static_cast<int>(k / a.nx);
     const int x = static_cast<int>(k - static_cast<int64_t>(y) * a.nx);
     const int n = y * a.pitch + x;
-    const T phi = static_cast<T>(phi0[k]);
-    T Bx = phi * fmadd(T(0.5) * a.bx, phi, a.ax), By = phi * fmadd(T(0.5) * a.by, phi, a.ay);
-    if (a.fcx != T(0) || a.fcy != T(0)) {
-        const T pw = abspow(phi, a.fq);
-        Bx = fmadd(a.fcx, pw, Bx);
-        By = fmadd(a.fcy, pw, By);
-    }
+    const double p = phi0[k];
+    double Bx, By;
+    init_flux(p, c.ab, c.cq, Bx, By);
     T* const in = const_cast<T*>(a.fin);
     T* const phi_in = const_cast<T*>(a.phi_prev);
-    a.phi_out[n] = phi_in[n] = phi;
-    a.fout[kMomQx * a.plane + n] = in[kMomQx * a.plane + n] = Bx;
-    a.fout[kMomQy * a.plane + n] = in[kMomQy * a.plane + n] = By;
+    a.phi_out[n] = phi_in[n] = static_cast<T>(p);
+    a.fout[kMomQx * a.plane + n] = in[kMomQx * a.plane + n] = static_cast<T>(Bx);
+    a.fout[kMomQy * a.plane + n] = in[kMomQy * a.plane + n] = static_cast<T>(By);
     if (a.mom_g) {
-        T s = kind != kSrcNone ? mom_source(a, n, x, y) : T(0);
-        if (a.rr != T(0)) s = s + (a.rr * phi) * (T(1) - abspow(phi, a.rp));
-        a.fout[kMomG * a.plane + n] = in[kMomG * a.plane + n] = phi + s;
+        double s = kind != kSrcNone ? static_cast<double>(mom_source(a, n, x, y)) : 0.0;
+        if (a.rr != T(0)) s += static_cast<double>(a.rr) * p * (1.0 - pow(fabs(p), static_cast<double>(a.rp)));
+        a.fout[kMomG * a.plane + n] = in[kMomG * a.plane + n] = static_cast<T>(p + s);
     }
 }
 
@@ -109,10 +107,10 @@ __device__ __forceinline__ typename F::T population_at(const GatherArgs<typename
         if (a.mom) {
             if (a.fresh) {
                 const int n = y * a.s.pitch + x;
-                const T* q = a.s.fin;
-                const T w = i == 0 ? Lat<T>::w0 : (i < 5 ? Lat<T>::w1 : Lat<T>::w5);
-                return w * fmadd(T(3), T(dir_cx(i)) * q[kMomQx * a.s.plane + n] + T(dir_cy(i)) * q[kMomQy * a.s.plane + n],
-                                 a.s.phi_prev[n]);
+                const double w = i == 0 ? Lat<double>::w0 : (i < 5 ? Lat<double>::w1 : Lat<double>::w5);
+                const double cq = dir_cx(i) * static_cast<double>(a.s.fin[kMomQx * a.s.plane + n]) +
+                                  dir_cy(i) * static_cast<double>(a.s.fin[kMomQy * a.s.plane + n]);
+                return static_cast<T>(w * (static_cast<double>(a.s.phi_prev[n]) + 3.0 * cq));
             }
             return a.s.wtab != nullptr ? mom_population<T, true>(a.s, x, y, i) : mom_population<T, false>(a.s, x, y, i);
         }
@@ -217,15 +215,21 @@ __global__ __launch_bounds__(kBlock) void reduce_final_kernel(const double* __re
 
 inline unsigned blocks_for(int64_t n) { return static_cast<unsigned>((n + kBlock - 1) / kBlock); }
 
+InitConsts flux_consts(const double ab[4], const double cq[3])
+{
+    InitConsts c{};
+    for (int q = 0; q < 4; ++q) c.ab[q] = ab[q];
+    for (int q = 0; q < 3; ++q) c.cq[q] = cq[q];
+    return c;
+}
+
 template <typename F>
 hipError_t init_with(const SweepArgs<typename F::T>& a, const double* phi0, const double wall[4], const double ab[4],
                      const double cq[3], const double dq[4], hipStream_t s)
 {
     const int64_t nn = static_cast<int64_t>(a.nx) * a.ny;
-    InitConsts c{};
+    InitConsts c = flux_consts(ab, cq);
     for (int q = 0; q < 4; ++q) c.wall[q] = wall[q];
-    for (int q = 0; q < 4; ++q) c.ab[q] = ab[q];
-    for (int q = 0; q < 3; ++q) c.cq[q] = cq[q];
     for (int q = 0; q < 4; ++q) c.dq[q] = dq[q];
     hipLaunchKernelGGL((init_kernel<F>), dim3(blocks_for(nn)), dim3(kBlock), 0, s, a, phi0, c);
     return hipGetLastError();
@@ -352,10 +356,11 @@ hipError_t launch_init(const SweepArgs<T>& a, int fmt, const double* phi0, const
 }
 
 template <typename T>
-hipError_t launch_mom_init(const SweepArgs<T>& a, int kind, const double* phi0, hipStream_t s)
+hipError_t launch_mom_init(const SweepArgs<T>& a, int kind, const double* phi0, const double ab[4], const double cq[3],
+                           hipStream_t s)
 {
     const int64_t nn = static_cast<int64_t>(a.nx) * a.ny;
-    hipLaunchKernelGGL((mom_init_kernel<T>), dim3(blocks_for(nn)), dim3(kBlock), 0, s, a, kind, phi0);
+    hipLaunchKernelGGL((mom_init_kernel<T>), dim3(blocks_for(nn)), dim3(kBlock), 0, s, a, kind, phi0, flux_consts(ab, cq));
     return hipGetLastError();
 }
 
@@ -386,7 +391,8 @@ hipError_t launch_convert(const double* in, T* out, int nx, int ny, int pitch, h
     template LaunchCfg resolve_launch<T>(const SweepArgs<T>&, int, int, int, LaunchCfg);                         \
     template hipError_t launch_init<T>(const SweepArgs<T>&, int, const double*, const double[4], const double[4],  \
                                        const double[3], const double[4], hipStream_t);                             \
-    template hipError_t launch_mom_init<T>(const SweepArgs<T>&, int, const double*, hipStream_t);                 \
+    template hipError_t launch_mom_init<T>(const SweepArgs<T>&, int, const double*, const double[4], const double[3],  \
+                                           hipStream_t);                                                           \
     template hipError_t launch_gather_field<T>(const GatherArgs<T>&, int, hipStream_t);                           \
     template hipError_t launch_reduce<T>(const GatherArgs<T>&, int, int, double*, hipStream_t);                   \
     template hipError_t launch_convert<T>(const double*, T*, int, int, int, hipStream_t);                         \

@@ -11,6 +11,7 @@ import pytest
 from paper_1902_09813_amd import btrt, btrt3
 from paper_1902_09813_amd import workloads as W
 from tests._cases import normwise, run_oracle3
+from tests._paper3 import C3
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +49,24 @@ def test_shapes_against_one_step_and_the_oracle(size, bc):
                         assert normwise(got[0], run_oracle3(w, 0).f) <= 1e-15
                         assert normwise(got[1], o.f) <= 1e-12 and normwise(got[2], o.phi()) <= 1e-12
                 assert all(np.array_equal(x, y) for x, y in zip(got, want)), (shape, precision)
+
+
+@pytest.mark.parametrize("precision,u", [(btrt.F32, 2.0 ** -24), (btrt.F64, 2.0 ** -53)])
+def test_initial_state_is_rounded_once(precision, u):
+    # As in two dimensions (flux coefficients that FP32 holds exactly).
+    c = np.rint(C3).astype(int)
+    rng = np.random.default_rng(2)
+    phi0 = rng.random((30, 31, 33))
+    a, b = (0.03125, -0.015625, 0.0078125), (0.0625, 0.03125, -0.046875)
+    with btrt3.Solver3(btrt3.Problem3(33, 31, 30, flux_a=a, flux_b=b, A0=(0.05, 0.01, 0.005, 0.04, -0.008, 0.03),
+                                      precision=precision), phi0) as s:
+        phi, f = s.field(), s.populations()
+    assert np.array_equal(phi, phi0 if precision == btrt.F64 else phi0.astype(np.float32).astype(np.float64))
+    p = phi0.astype(np.longdouble)
+    B = [p * (a[k] + 0.5 * b[k] * p) for k in range(3)]
+    ops = 8 if precision == btrt.F64 else 1.0001
+    for i in range(19):
+        wt = np.longdouble(1) / (3, 18, 36)[int(np.sum(np.abs(c[i])))]
+        feq = wt * (p + 3 * sum(int(c[i][k]) * B[k] for k in range(3)))
+        bound = ops * u * (wt * (np.abs(p) + 3 * sum(np.abs(c[i][k] * B[k]) for k in range(3))) + np.abs(feq))
+        assert np.all(np.abs(f[i] - feq) <= bound), (i, precision)

@@ -66,6 +66,32 @@ def test_every_walk_against_one_step_and_the_oracle(size, bc):
                 assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), (k, precision)
 
 
+@pytest.mark.parametrize("precision,u", [(btrt.F32, 2.0 ** -24), (btrt.F16DEV, 2.0 ** -24), (btrt.F64, 2.0 ** -53)])
+def test_initial_state_is_rounded_once(precision, u):
+    # f(0) = w (phi0 + 3 c . B(phi0)) evaluated in FP64: phi and q are rounded once each on the way in and f
+    # once on the way out, relative u each. (B evaluated in FP32 misses this at one node in 400.) FP64 reads
+    # are compared with a longer reference.
+    nx, ny = 130, 120
+    for kw in (dict(), dict(flux_c=(0.02, -0.03), flux_q=2.5)):
+        if kw and precision == btrt.F16DEV:
+            continue  # the 16-bit formats refuse a power-law flux
+        w = case(nx, ny, BCS["periodic"], **kw)
+        phi0 = w.phi0()
+        with btrt.Solver(btrt.problem_from_workload(w, precision=precision), phi0) as s:
+            phi, f = s.field(), s.populations()
+        assert np.array_equal(phi, phi0 if precision == btrt.F64 else phi0.astype(np.float32).astype(np.float64))
+        p = phi0.astype(np.longdouble)
+        c, q = kw.get("flux_c", (0.0, 0.0)), kw.get("flux_q", 1.0)
+        B = [p * (w.flux_a[k] + 0.5 * w.flux_b[k] * p) + c[k] * np.abs(p) ** q for k in (0, 1)]
+        # In FP64 the evaluation itself rounds: a handful of operations (the power among them) instead of none.
+        ops = 8 if precision == btrt.F64 else 1.0001
+        for i, (cx, cy) in enumerate(((0, 0), (1, 0), (0, 1), (-1, 0), (0, -1), (1, 1), (-1, 1), (-1, -1), (1, -1))):
+            wt = np.longdouble(1) / (9 if i < 5 else 36) * (4 if i == 0 else 1)
+            feq = wt * (p + 3 * (cx * B[0] + cy * B[1]))
+            bound = ops * u * (wt * (np.abs(p) + 3 * (np.abs(cx * B[0]) + np.abs(cy * B[1]))) + np.abs(feq))
+            assert np.all(np.abs(f[i] - feq) <= bound), (i, kw, precision)
+
+
 def test_general_model_with_unit_rates():
     w = dataclasses.replace(W.bfe(n=17, t_end=0.4), k2=1.0)
     say(f"[gpu] moments, general model {w.nx}x{w.ny} steps {w.steps}")
