@@ -1,0 +1,61 @@
+"""The library's host code where something goes wrong or runs on a special stream, without a GPU: in a process
+of its own against a stand-in for the HIP runtime (tests/fake_hip/fake_hip.c: device memory is host memory,
+kernels do nothing), which can refuse a copy and count the launches of other threads."""
+import os
+import shutil
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+HIP = os.environ.get("ROCM_PATH", "/opt/rocm") + "/include"
+
+pytestmark = pytest.mark.skipif(shutil.which("gcc") is None or not os.path.isdir(HIP), reason="no gcc or HIP headers")
+
+PRELUDE = """
+import ctypes, sys
+sys.modules["torch"] = None  # the stand-in is the only runtime here
+sys.path.insert(0, {root!r})
+fake = ctypes.CDLL({lib!r}, mode=ctypes.RTLD_GLOBAL)
+fake.fake_watch.argtypes = [ctypes.c_void_p]
+import numpy as np
+from paper_1902_09813_amd import btrt, btrt3
+"""
+
+
+@pytest.fixture(scope="module")
+def fake_lib(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake_hip") / "libfake_hip.so")
+    subprocess.run(["gcc", "-O1", "-std=c11", "-shared", "-fPIC", "-pthread", "-I", HIP,
+                    os.path.join(HERE, "fake_hip", "fake_hip.c"), "-o", out], check=True, capture_output=True, text=True)
+    return out
+
+
+def run(fake_lib, body):
+    res = subprocess.run([sys.executable, "-c", PRELUDE.format(root=ROOT, lib=fake_lib) + body], capture_output=True,
+                         text=True, timeout=120)
+    assert res.returncode == 0 and res.stdout.strip().endswith("done"), res.stdout + res.stderr
+
+
+def test_reads_on_the_per_thread_stream_stay_on_the_calling_thread(fake_lib):
+    # hipStreamPerThread (2) is another stream in each thread: a copy launched by a helper thread would not be
+    # ordered behind the caller's work. Any other stream is shared out.
+    run(fake_lib, """
+seen = []
+for stream in (0x1000, 2):
+    p = btrt.Problem(700, 600, A0=(0.01, 0.0, 0.01))
+    p.grid.stream = stream
+    p3 = btrt3.Problem3(96, 80, 70, A0=(0.05, 0.01, 0.005, 0.04, -0.008, 0.03))
+    p3.grid.stream = stream
+    phi0, phi3 = np.zeros((600, 700)), np.zeros((70, 80, 96))
+    with btrt.Solver(p, phi0) as s, btrt3.Solver3(p3, phi3) as s3, btrt.Batch([(p, phi0)], stream=stream) as b:
+        for read in (s.field, s3.field, lambda: b.field(0)):
+            fake.fake_watch(stream)
+            read()
+            seen.append((fake.fake_launches(), fake.fake_foreign_launches()))
+assert all(t > 3 and f > 0 for t, f in seen[:3]), seen
+assert all(t > 3 and f == 0 for t, f in seen[3:]), seen
+print("done")
+""")
