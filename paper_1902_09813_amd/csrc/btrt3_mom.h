@@ -25,6 +25,7 @@
 #pragma once
 
 #include "btrt3_internal.h"
+#include "btrt_recip.h"
 
 namespace btrt3k {
 
@@ -190,16 +191,7 @@ __host__ __device__ __forceinline__ Mom3State<T> mom3_collide(const Sweep3<T>& a
         const T c13 = fma3(m12, m23, -(m13 * m22)), c22 = fma3(m11, m33, -(m13 * m13));
         const T c23 = fma3(m12, m13, -(m11 * m23)), c33 = fma3(m11, m22, -(m12 * m12));
         const T det = fma3(m11, c11, fma3(m12, c12, m13 * c13));
-#if defined(__HIP_DEVICE_COMPILE__)
-        T r;
-        if constexpr (sizeof(T) == 4) r = __builtin_amdgcn_rcpf(det); else r = __builtin_amdgcn_rcp(det);
-#else
-        T r = T(1) / det;
-#endif
-        // The hardware reciprocal and one (FP32) or two (FP64) Newton steps: a correctly rounded 1/det but
-        // for rare ties (measured for the two-dimensional form, whose det M has the same range below).
-        r = fma3(r, fma3(-det, r, T(1)), r);
-        if constexpr (sizeof(T) == 8) r = fma3(r, fma3(-det, r, T(1)), r);
+        const T r = btrtk::quotient(det);
         o.qx = fma3(-r, fma3(c11, h[0], fma3(c12, h[1], c13 * h[2])), v[0]);
         o.qy = fma3(-r, fma3(c12, h[0], fma3(c22, h[1], c23 * h[2])), v[1]);
         o.qz = fma3(-r, fma3(c13, h[0], fma3(c23, h[1], c33 * h[2])), v[2]);

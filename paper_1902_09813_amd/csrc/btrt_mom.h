@@ -30,6 +30,7 @@
 #pragma once
 
 #include "btrt_device.h"
+#include "btrt_recip.h"
 
 namespace btrtk {
 
@@ -191,7 +192,12 @@ __host__ __device__ __forceinline__ MomState<T> mom_collide(const SweepArgs<T>& 
         const T m11 = fmadd(a11, g, half);
         const T m12 = a12 * g;
         const T m22 = fmadd(a22, g, half);
-        const T rdet = recip<T, true>(fmadd(m11, m22, -(m12 * m12)));
+        const T det = fmadd(m11, m22, -(m12 * m12));
+        T rdet;  // as in the population form: the quotient in FP32, two Newton steps in FP64
+        if constexpr (sizeof(T) == 4)
+            rdet = quotient(det);
+        else
+            rdet = recip(det);
         const T ux = fmadd(m22, hx, -(m12 * hy));
         const T uy = fmadd(m11, hy, -(m12 * hx));
         o.qx = fmadd(-rdet, ux, jx + dBx);

@@ -33,9 +33,10 @@ __host__ __device__ inline T abspow(T x, T y)
 // walkers where every level repeats it; measured on gfx950 over 2^24 divisors log-uniform in
 // [1/4, 64), it gives the IEEE quotient every time (the reciprocal alone is off by up to 2.5e8
 // ulp, one Newton step by up to 11). FP32: a division,
-// or with ONE_NEWTON the hardware reciprocal and one Newton step (within an ulp, a third of the
-// instructions; the 16-bit deviation formats, whose walkers keep the VALU busy every cycle, run
-// 5-6.5 % faster with it, while the FP32 seven-step walker's schedule ran 2 % slower).
+// or with ONE_NEWTON the hardware reciprocal and one Newton step (the same bits up to d = 2^126, see
+// btrt_recip.h, in a third of the instructions, but NaN where d is infinite; the 16-bit deviation formats,
+// whose walkers keep the VALU busy every cycle, run 5-6.5 % faster with it, while the FP32 seven-step
+// walker's schedule ran 2 % slower).
 template <typename T, bool ONE_NEWTON = false>
 __host__ __device__ inline T recip(T d)
 {

@@ -70,3 +70,20 @@ def test_initial_state_is_rounded_once(precision, u):
         feq = wt * (p + 3 * sum(int(c[i][k]) * B[k] for k in range(3)))
         bound = ops * u * (wt * (np.abs(p) + 3 * sum(np.abs(c[i][k] * B[k]) for k in range(3))) + np.abs(feq))
         assert np.all(np.abs(f[i] - feq) <= bound), (i, precision)
+
+
+@pytest.mark.parametrize("precision,scale,tol", [(btrt.F32, 1e14, 1e-5), (btrt.F64, 1e104, 1e-12)])
+def test_determinant_beyond_the_range(precision, scale, tol):
+    # det M overflows (3e38, 1.8e308) while M and its cofactors do not: 1/det M is 0 as a division gives it.
+    # The oracle runs the diffusion tensor scaled down by what keeps K1 below one rounding of everything else.
+    def run(factor):
+        w = box(33, 20, 9, (0,) * 6, False, 0.5)
+        w.A0 = tuple(factor * v for v in w.A0)
+        return w
+    want = run_oracle3(run(min(scale, 1e80))).phi()
+    w = run(scale)
+    for shape in [(1, 0, 0), (2, 0, 0)]:
+        with btrt3.Solver3(btrt3.problem_from_workload3(w, precision=precision), w.phi0()) as s:
+            s.set_launch(*shape)
+            phi = s.step(w.steps).field()
+        assert normwise(phi, want) <= tol, shape

@@ -92,6 +92,17 @@ def test_initial_state_is_rounded_once(precision, u):
             assert np.all(np.abs(f[i] - feq) <= bound), (i, kw, precision)
 
 
+def test_determinant_beyond_the_range_of_fp32():
+    # K1 = adj(M) / det M per node: det M overflows FP32 (3e38) while M does not, and 1/det M is then 0 as a
+    # division gives it (K1 itself is below 1e-19), not NaN.
+    w = dataclasses.replace(case(70, 40, BCS["periodic"], beta=0.5), A0=(1e19, 0.0, 2e19))
+    o = run_oracle(w, 9)
+    for k in (1, 0, 4):
+        with btrt.Solver(btrt.problem_from_workload(w, precision=btrt.F32), w.phi0()) as s:
+            phi = s.set_launch(k, 0, 0, 0).step(9).field()
+        assert normwise(phi, o.phi()) <= 1e-5, k
+
+
 def test_general_model_with_unit_rates():
     w = dataclasses.replace(W.bfe(n=17, t_end=0.4), k2=1.0)
     say(f"[gpu] moments, general model {w.nx}x{w.ny} steps {w.steps}")
