@@ -211,7 +211,8 @@ int btrt_step(btrt_t* h, int64_t n);
  * 2j + 1 + c_y, through a y side sample 2i + 1 + c_x, and a diagonal link through a corner point
  * the mean of the two sides' samples there. The values are copied (host memory, read during the
  * call); the handle allocates device memory for them ((P + 4) * (steps + 1) values, the corner
- * means included; freed by the next call or btrt_destroy).
+ * means included) and keeps it and that of the call before, which the next call fills again where
+ * it is large enough, until btrt_destroy. A call that fails leaves the values in force as they are.
  * Once set, btrt_step, btrt_solve and btrt_tune may advance at most `steps` steps past the
  * step count of this call; a new call continues from the current step. Selects the general
  * node model from the next step on. Errors: BTRT_E_INVAL for NULL values, steps < 1,

@@ -25,8 +25,10 @@ struct btrt {
     bool own_mem = false;
     int check_interval = 1000;
     btrtk::LaunchCfg launch{};  // requested launch shape (zero fields: automatic)
-    void* wsched = nullptr;     // device wall schedule of btrt_set_walls (owned), of wsched_bytes bytes
+    void* wsched = nullptr;     // device wall schedule in force (owned), of wsched_bytes bytes
     size_t wsched_bytes = 0;
+    void* wspare = nullptr;     // the schedule before it: the next call of btrt_set_walls fills it if it fits
+    size_t wspare_bytes = 0;
     StagingUser staging;
     Instance inst;
 };
@@ -73,6 +75,7 @@ void release(btrt* h)
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     if (h->own_mem && h->mem) (void)hipFree(h->mem);
     if (h->wsched) (void)hipFree(h->wsched);
+    if (h->wspare) (void)hipFree(h->wspare);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
     delete h;
 }
@@ -376,35 +379,40 @@ int btrt_set_walls(btrt_t* h, const double* values, int64_t steps)
     const size_t bytes = static_cast<size_t>(S) * static_cast<size_t>(steps + 1) * es;
     DeviceGuard g(h->device);
     if (g.status() != hipSuccess) return hip_fail(g.status(), "hipSetDevice");
-    // The table of an earlier call serves again where it is large enough: what it still feeds is ahead
-    // of the new values on the stream.
-    void* mem = h->wsched;
-    const bool fresh = !mem || h->wsched_bytes < bytes;
-    if (fresh && hipMalloc(&mem, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(BTRT_E_NOMEM, "hipMalloc of %zu bytes for the wall schedule failed", bytes);
+    // The new values go into the table before the one in force, if it is large enough, else into a new one: a
+    // call that fails leaves the schedule in force as it is. (What the spare table once fed is ahead of the new
+    // values on the stream.)
+    const bool reuse = h->wspare && h->wspare_bytes >= bytes;
+    if (!reuse) {
+        if (h->wspare) {
+            (void)hipStreamSynchronize(h->stream);  // a launch may still read it
+            (void)hipFree(h->wspare);
+            h->wspare = nullptr;
+        }
+        if (hipMalloc(&h->wspare, bytes) != hipSuccess) {
+            h->wspare = nullptr;
+            (void)hipGetLastError();
+            return fail(BTRT_E_NOMEM, "hipMalloc of %zu bytes for the wall schedule failed", bytes);
+        }
+        h->wspare_bytes = bytes;
     }
-    char* dst = static_cast<char*>(mem);
+    char* dst = static_cast<char*>(h->wspare);
     // Entry 0: the values the next pull reads (the step that ends at the current count), from
     // the current table, or the per-side constants the populations were initialised with.
-    hipError_t e = hipSuccess;
+    hipError_t e;
     if (I.gen && I.wtab) {
         const char* cur = I.wtab + static_cast<size_t>(I.step - I.wall_t0) * I.wall_stride * es;
-        if (cur != dst) e = hipMemcpyAsync(dst, cur, static_cast<size_t>(S) * es, hipMemcpyDeviceToDevice, h->stream);
+        e = hipMemcpyAsync(dst, cur, static_cast<size_t>(S) * es, hipMemcpyDeviceToDevice, h->stream);
     } else {
         e = upload_wall_entry(I, dst, h->stream);
     }
     if (e == hipSuccess) e = upload_wall_values(I, values, static_cast<size_t>(steps), dst + S * es, h->stream);
     if (e != hipSuccess) {
         (void)hipStreamSynchronize(h->stream);
-        if (fresh) (void)hipFree(mem);
         return hip_fail(e, "wall schedule upload");
     }
-    if (fresh) {
-        if (h->wsched) (void)hipFree(h->wsched);  // the stream is idle: nothing reads it any more
-        h->wsched = mem;
-        h->wsched_bytes = bytes;
-    }
+    std::swap(h->wsched, h->wspare);
+    std::swap(h->wsched_bytes, h->wspare_bytes);
     I.gen = true;
     I.wtab = dst;
     I.wall_t0 = I.step;

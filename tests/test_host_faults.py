@@ -59,3 +59,52 @@ assert all(t > 3 and f > 0 for t, f in seen[:3]), seen
 assert all(t > 3 and f == 0 for t, f in seen[3:]), seen
 print("done")
 """)
+
+
+def test_a_wall_schedule_whose_upload_fails_leaves_the_old_one_in_force(fake_lib):
+    # 500 rows go up in three pieces behind the copy of the row in force; each of the four copies fails once.
+    # The values in force at every later step (in the checkpoint's last bytes) stay those of the old schedule.
+    run(fake_lib, """
+n, rows = 40, 500
+P = 4 * (n + n) + 4
+rng = np.random.default_rng(1)
+first, second, third = rng.random((3, rows, P))
+
+def solver():
+    return btrt.Solver(btrt.Problem(n, n, A0=(0.01, 0.0, 0.01), bc_type=(1,) * 4, bc_value=(0.1, 0.2, 0.3, 0.4)),
+                       np.zeros((n, n)))
+
+def entries(s, steps):
+    out = []
+    for _ in range(steps):
+        out.append(s.step(1).checkpoint()[-8 * (P + 4):])
+    return out
+
+with solver() as s, solver() as ref:
+    for x in (s, ref):
+        x.set_walls(first).step(7)
+    for round in range(2):
+        for k in range(4):
+            fake.fake_fail_copy(k)
+            try:
+                s.set_walls(second)
+            except btrt.BtrtError as e:
+                assert e.code == btrt.E_DEVICE, e
+            else:
+                raise AssertionError("no failure at copy %d" % k)
+            fake.fake_fail_copy(-1)
+        assert entries(s, 150) == entries(ref, 150), round
+        want = first if round == 0 else third
+        assert s.checkpoint()[-8 * (P + 4):][:8 * P] == want[(157 if round == 0 else 150) - 1].tobytes()
+        for x in (s, ref):
+            x.set_walls(third)
+    for x in (s, ref):
+        x.set_walls(first).step(rows)
+        try:
+            x.step(1)
+        except btrt.BtrtError as e:
+            assert e.code == btrt.E_INVAL
+        else:
+            raise AssertionError("stepped past the schedule")
+print("done")
+""")
