@@ -41,10 +41,16 @@ CHECK_INTERVAL = 1000
 METRIC = "MLUPS and % HBM roofline, batched/served vs plain; p50/p99 solve latency"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_traffic.json")
 CSRC = os.path.join(ROOT, "paper_1902_09813_amd", "csrc")
-KERNEL_SOURCES = ("btrt_mom.h", "btrt_mom_tile.h", "btrt_mom_f64.hip", "btrt_mom_f32.hip", "btrt_internal.h", "btrt_node.h", "btrt_device.h", "btrt_sweep_f64.hip", "btrt_sweep_f32.hip",
+KERNEL_SOURCES = ("btrt_internal.h", "btrt_node.h", "btrt_recip.h", "btrt_device.h", "btrt_mom.h", "btrt_mom_tile.h",
+                  "btrt_mom_f64.hip", "btrt_mom_f32.hip", "btrt_mom_gen_f64.hip", "btrt_mom_gen_f32.hip",
+                  "btrt_sweep_f64.hip", "btrt_sweep_f32.hip", "btrt_sweep_gen_f64.hip", "btrt_sweep_gen_f32.hip",
                   "btrt_sweep_k0_f64.hip", "btrt_sweep_k0_f32.hip", "btrt_sweep_k0_f16dev.hip",
                   "btrt_sweep_k0_bf16dev.hip", "btrt_sweep_f16dev.hip", "btrt_sweep_bf16dev.hip",
-                  "btrt_batch_kernels.hip", "btrt_kernels.hip")
+                  "btrt_mom_batch.h", "btrt_mom_batch.hip", "btrt_batch_kernels.hip", "btrt_kernels.hip",
+                  "btrt3_internal.h", "btrt3_mom.h", "btrt3_mom.hip", "btrt3_kernels.hip")
+# The kernels by btrt_get_sweep's number and by the state they keep (populations, moments).
+SWEEP_KERNELS = (("sweep_kernel", "mom_sweep_kernel"), ("sweep2_kernel", None), ("walk_kernel", "mom_walk_kernel"),
+                 ("block_kernel", "mom_block_kernel"), (None, "mom_region_kernel"))
 
 
 def kernel_hash() -> str:
@@ -67,14 +73,6 @@ def sweep_launches(steps, fusion):
     return n
 
 
-def state_bytes(w, info):
-    """Bytes a launch reads and writes per node: with k0 = K2 = 1 the state is phi and the first moments
-    (and g with a source) in the format computed in, FP64 or FP32, else what the library reports."""
-    if w.k0 != 1.0 or w.k2 != 1.0:
-        return info.bytes_per_node_launch
-    return 2.0 * (4 if w.source is not None else 3) * (8 if info.bytes_per_node_launch == 160 else 4)
-
-
 def timed_run(w, precision, steps, warmup, fusion=0, launch=None):
     """Warm up, then time exactly ``steps`` steps with HIP events on the library's stream.
 
@@ -87,7 +85,6 @@ def timed_run(w, precision, steps, warmup, fusion=0, launch=None):
     prob = btrt.problem_from_workload(w, precision=precision, check_interval=CHECK_INTERVAL)
     solver = btrt.Solver(prob, w.phi0(), torch_memory=True)  # torch memory + a torch stream
     stream = solver.torch_stream  # the stream every kernel of the solver is launched on
-    info = solver.info()
     tuned = 0
     if launch:
         solver.set_launch(*launch)
@@ -95,8 +92,8 @@ def timed_run(w, precision, steps, warmup, fusion=0, launch=None):
         solver.set_fusion(fusion)
     else:
         _, tuned = solver.tune(900)
-    shape = solver.launch()
-    fusion = shape[0]
+    shape, sweep = solver.launch(), solver.sweep()
+    fusion = sweep["steps_per_launch"]
     solver.step(max(0, warmup - tuned))
     solver.sync()
     torch.cuda.synchronize()
@@ -135,7 +132,8 @@ def timed_run(w, precision, steps, warmup, fusion=0, launch=None):
         "launches": sweep_launches(steps, fusion),
         "launch_ms_avg": sweep_ms / sweep_launches(steps, fusion),
         "mlups": nodes * steps / (total_ms * 1e-3) / 1e6,
-        "bytes_per_node_launch": state_bytes(w, info),
+        "bytes_per_node_launch": sweep["bytes_per_node"],
+        "sweep": dict(sweep, kernel=SWEEP_KERNELS[sweep["kernel"]][sweep["moments"]]),
         "nodes": nodes,
         "residual": residual,
         "launch": {"steps_per_launch": shape[0], "strip_rows": shape[1], "strips_per_group": shape[2],
@@ -400,13 +398,13 @@ def cpu_baseline(w3, w2, steps3=30, steps2=200, steps3_1=3, steps2_1=20, runs=3)
     }
 
 
-def traffic_key(precision_name, launch):
-    return (f"{precision_name}_k{launch['steps_per_launch']}_r{launch['strip_rows']}"
-            f"_g{launch['strips_per_group']}_t{launch['tile']}")
+def traffic_key(precision_name, sweep):
+    """Key of a launch in the counter record: storage, kernel, steps and the nodes its units write."""
+    return f"{precision_name}_{sweep['kernel']}_k{sweep['steps_per_launch']}_{sweep['columns']}x{sweep['rows']}"
 
 
-def counter_record(precision_name, nodes, launch):
-    """The committed rocprofv3 counter figures of one launch shape, or None if the kernel source
+def counter_record(precision_name, nodes, sweep):
+    """The committed rocprofv3 counter figures of one kernel and shape, or None if the kernel source
     changed since the counters were taken or that shape was not measured on this grid."""
     try:
         with open(TRAFFIC_FILE) as fh:
@@ -415,29 +413,29 @@ def counter_record(precision_name, nodes, launch):
         return None
     if rec.get("kernel_sha256_16") != kernel_hash():
         return None
-    ent = rec.get(traffic_key(precision_name, launch))
+    ent = rec.get(traffic_key(precision_name, sweep))
     if not ent or ent.get("nodes") != nodes:
         return None
     return ent
 
 
-def traffic_for(precision_name, nodes, launch):
+def traffic_for(precision_name, nodes, sweep):
     """HBM bytes per sweep launch (FETCH_SIZE and WRITE_SIZE, scaled by a plain copy), or None."""
-    ent = counter_record(precision_name, nodes, launch)
+    ent = counter_record(precision_name, nodes, sweep)
     return None if ent is None else ent.get("bytes_per_launch")
 
 
-def valu_busy_for(precision_name, nodes, launch):
+def valu_busy_for(precision_name, nodes, sweep):
     """Fraction of SIMD cycles with a VALU instruction in flight (SQ_ACTIVE_INST_VALU x 4 over
     1024 SIMDs x GRBM_GUI_ACTIVE per XCD), or None if not measured for this shape and source."""
-    ent = counter_record(precision_name, nodes, launch)
+    ent = counter_record(precision_name, nodes, sweep)
     return None if ent is None else ent.get("valu_busy")
 
 
-def valu_lanes_for(precision_name, nodes, launch):
+def valu_lanes_for(precision_name, nodes, sweep):
     """VALU lane-instructions per node update (SQ_INSTS_VALU x 64 over the launch's updates), or
     None if not measured for this shape and source."""
-    ent = counter_record(precision_name, nodes, launch)
+    ent = counter_record(precision_name, nodes, sweep)
     return None if ent is None else ent.get("valu_lane_instructions_per_update")
 
 
@@ -450,22 +448,24 @@ def roofline_of(r, precision_name):
     (FP32 arithmetic, issued at the FP64 rate when not packed): achieved = the VALU lane-
     instructions the counter record measured for the shape / launch time against the issue peak
     (HBM as the bound when no record covers the shape). The HBM figures stand beside it."""
-    k = r["launch"]["steps_per_launch"]
+    sweep = r["sweep"]
+    k = sweep["steps_per_launch"]
     t = r["launch_ms_avg"] * 1e-3
     nodes = r["nodes"]
     bytes_per_launch = r["bytes_per_node_launch"] * nodes
     hbm_launch = bytes_per_launch / t / 1e9
     out = {
-        "kernel": "sweep_kernel" if k == 1 else ("sweep2_kernel" if r["launch"]["tile"] else "walk_kernel"),
-        "traffic": traffic_for(precision_name, nodes, r["launch"]),
-        "valu_busy": valu_busy_for(precision_name, nodes, r["launch"]),
+        "kernel": sweep["kernel"],
+        "traffic": traffic_for(precision_name, nodes, sweep),
+        "valu_busy": valu_busy_for(precision_name, nodes, sweep),
         "launch": r["launch"],
+        "sweep": sweep,
         "launch_us_avg": round(t * 1e6, 2),
         "hbm_per_launch": {"achieved": round(hbm_launch, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                            "frac": round(hbm_launch / HBM_PEAK_GBS, 4), "bytes_per_launch": bytes_per_launch},
     }
     updates = nodes * k
-    lanes = valu_lanes_for(precision_name, nodes, r["launch"]) if k > 1 and precision_name != "f64" else None
+    lanes = valu_lanes_for(precision_name, nodes, sweep) if k > 1 and precision_name != "f64" else None
     if lanes is not None:
         issue = lanes * updates / t / 1e12
         out.update({"bound": "alu", "achieved": round(issue, 2), "peak": FP64_ISSUE_PEAK_T,

@@ -241,7 +241,8 @@ int btrt_set_walls(btrt_t* h, const double* values, int64_t steps);
  *                     several of the steps of one btrt_step call in each launch
  *   strips_per_group  1 or 4 strips per workgroup, walked side by side (0: auto)
  *   tile              1 with steps_per_launch 2: the two-step LDS tile kernel instead of a
- *                     strip walker (tiles of 64 x 8 nodes in FP64, 64 x 16 otherwise) */
+ *                     strip walker (tiles of 64 x 8 nodes in FP64, 64 x 16 otherwise; with k0 = 1 and
+ *                     K2 = 1 a strip walker all the same, strips as high as those tiles) */
 typedef struct {
     int32_t steps_per_launch;
     int32_t strip_rows;
@@ -254,8 +255,47 @@ typedef struct {
  * 0, 1 or 4, tile without steps_per_launch 2). */
 int btrt_set_launch(btrt_t* h, const btrt_launch_t* cfg);
 
-/* The launch shape in force, with the automatic fields resolved for this grid. */
+/* The launch shape in force in the terms of btrt_launch_t, with the automatic fields resolved for this
+ * grid. An automatic shape may run kernels that these terms do not name (blocks and regions, below
+ * 2^20 nodes and in the moment form): btrt_get_sweep tells what runs, and zeros passed to
+ * btrt_set_launch, not the shape reported here, make another handle run it. */
 int btrt_get_launch(btrt_t* h, btrt_launch_t* cfg);
+
+/* What a launch of btrt_step runs with the shape in force (a call's last launches may take fewer steps).
+ *   kernel            BTRT_SWEEP_STEP    one step on tiles of 64 x rows nodes
+ *                     BTRT_SWEEP_TILE    two steps on tiles in LDS
+ *                     BTRT_SWEEP_STRIPS  strips walked by one wavefront each
+ *                     BTRT_SWEEP_BLOCKS  regions of one node per thread
+ *                     BTRT_SWEEP_REGIONS regions of 64 columns by several rows per thread
+ *   steps_per_launch  time steps of a launch
+ *   columns, rows     nodes written per tile, strip or region (less where the grid ends; the first and
+ *                     last strips between y walls are about half as high in the moment form)
+ *   threads           threads per workgroup
+ *   moments           1: the state is phi and its first moments (k0 = 1 and K2 = 1), 0: the populations
+ *   automatic         1: the library's choice (btrt_set_launch with zeros, the default, or kept by
+ *                     btrt_tune), 0: a shape that was set; with 1 pass zeros to set it on another handle,
+ *                     with 0 what btrt_get_launch reports
+ *   bytes_per_node    HBM bytes per node of a launch: the state read and written once, and a source field
+ *                     and an A0 field when given */
+#define BTRT_SWEEP_STEP 0
+#define BTRT_SWEEP_TILE 1
+#define BTRT_SWEEP_STRIPS 2
+#define BTRT_SWEEP_BLOCKS 3
+#define BTRT_SWEEP_REGIONS 4
+typedef struct {
+    int32_t kernel;
+    int32_t steps_per_launch;
+    int32_t columns;
+    int32_t rows;
+    int32_t threads;
+    int32_t moments;
+    int32_t automatic;
+    int32_t reserved;
+    double bytes_per_node;
+} btrt_sweep_t;
+
+/* Errors: BTRT_E_STATE for a NULL handle, BTRT_E_INVAL for a NULL result. */
+int btrt_get_sweep(btrt_t* h, btrt_sweep_t* sweep);
 
 /* Shorthand for btrt_set_launch({steps_per_launch, 0, 0, 0}); steps_per_launch in [1, 7]
  * (BTRT_E_INVAL otherwise). */
@@ -269,7 +309,8 @@ int btrt_set_fusion(btrt_t* h, int32_t steps_per_launch);
  * automatic shape again, in turn, twice over, one untimed and two timed launches each (the first
  * pass may run while the GPU clocks still rise); as far as max_steps allows. The state advances by *steps_used steps (the same
  * bits btrt_step would give); the Eq. (64) snapshot is not touched. Synchronises. best (may be
- * NULL) receives the shape kept, resolved. */
+ * NULL) receives the shape kept, as btrt_get_launch then reports it (btrt_get_sweep: whether it is the
+ * automatic one). */
 int btrt_tune(btrt_t* h, int64_t max_steps, btrt_launch_t* best, int64_t* steps_used);
 
 /* phi(t) = sum_i f_i(x, t) (Eq. (9)) into phi_out[nx*ny]. Synchronises. */

@@ -108,19 +108,18 @@ int btrt3_create(const btrt3_grid_t* grid, const btrt3_flux_t* B, const btrt3_di
 int btrt3_step(btrt3_t* h, int64_t n);
 
 /* Launch shape of btrt3_step. Every shape gives bitwise identical results; only the speed differs.
- *   steps_per_launch  1 or 2 (0: automatic, 2 from 2^21 nodes up, else 1). With 2, a workgroup
+ *   steps_per_launch  1 or 2 (0: automatic: 2 on periodic boxes from 2^21 nodes up, with k0 = 1 and
+ *                     K2 = 1 from 2^20, else 1). With 2, a workgroup
  *                     owns an xy tile of columns plus a one-column halo ring and walks z over a
  *                     chunk of planes: step 1 of each plane goes to LDS, step 2 of the plane below
  *                     is computed from it, so the state is read and written once per two steps.
- *                     With k0 = 1 and K2 = 1 the automatic shape (0) takes the steps per launch that
- *                     suit the moments such a state is kept as, and with a Dirichlet face one step,
- *                     which is faster there; what is reported stays as above
  *   z_chunk           two-step launches: output planes per workgroup (0: automatic, the chunk of
  *                     16 .. 64 planes that needs the fewest rounds of resident workgroups times
- *                     planes walked, so the launch's last round is nearly full)
+ *                     planes walked, so the launch's last round is nearly full; with k0 = 1 and
+ *                     K2 = 1, where launches of one step walk chunks too, of 1 .. 256 planes)
  *   tile              two-step launches, threads per workgroup (output columns): 1 = 64 x 8
  *                     (62 x 6), 2 = 32 x 16 (30 x 14), 3 = 32 x 8 (30 x 6), 4 = 16 x 16 (14 x 14);
- *                     0: automatic (1) */
+ *                     0: automatic (1). With k0 = 1 and K2 = 1 there is one tile, 64 x 16 (60 x 12) */
 typedef struct {
     int32_t steps_per_launch;
     int32_t z_chunk;

@@ -25,7 +25,7 @@ K2_VALUE, K2_HBB = 0, 1
 
 # Every function include/btrt.h declares.
 EXPORTS = ("btrt_validate", "btrt_workspace_size", "btrt_create", "btrt_step", "btrt_set_walls", "btrt_set_launch",
-           "btrt_get_launch",
+           "btrt_get_launch", "btrt_get_sweep",
            "btrt_set_fusion", "btrt_tune", "btrt_field",
            "btrt_populations", "btrt_residual", "btrt_error", "btrt_solve", "btrt_sync",
            "btrt_get_info", "btrt_destroy", "btrt_strerror", "btrt_last_error",
@@ -91,6 +91,15 @@ class Launch(ctypes.Structure):
 
     def as_tuple(self):
         return (self.steps_per_launch, self.strip_rows, self.strips_per_group, self.tile)
+
+
+SWEEP_STEP, SWEEP_TILE, SWEEP_STRIPS, SWEEP_BLOCKS, SWEEP_REGIONS = range(5)
+
+
+class Sweep(ctypes.Structure):
+    _fields_ = [("kernel", ctypes.c_int32), ("steps_per_launch", ctypes.c_int32), ("columns", ctypes.c_int32),
+                ("rows", ctypes.c_int32), ("threads", ctypes.c_int32), ("moments", ctypes.c_int32),
+                ("automatic", ctypes.c_int32), ("reserved", ctypes.c_int32), ("bytes_per_node", ctypes.c_double)]
 
 
 class BatchConfig(ctypes.Structure):
@@ -163,6 +172,7 @@ def lib() -> ctypes.CDLL:
             "btrt_set_fusion": ([hp, ctypes.c_int32], ctypes.c_int),
             "btrt_set_launch": ([hp, P(Launch)], ctypes.c_int),
             "btrt_get_launch": ([hp, P(Launch)], ctypes.c_int),
+            "btrt_get_sweep": ([hp, P(Sweep)], ctypes.c_int),
             "btrt_tune": ([hp, ctypes.c_int64, P(Launch), P(ctypes.c_int64)], ctypes.c_int),
             "btrt_field": ([hp, dp], ctypes.c_int),
             "btrt_populations": ([hp, dp], ctypes.c_int),
@@ -344,6 +354,12 @@ class Solver:
         cfg = Launch()
         _check(lib().btrt_get_launch(self.h, ctypes.byref(cfg)), "btrt_get_launch")
         return cfg.as_tuple()
+
+    def sweep(self) -> dict:
+        """btrt_get_sweep: what a launch runs with the shape in force."""
+        s = Sweep()
+        _check(lib().btrt_get_sweep(self.h, ctypes.byref(s)), "btrt_get_sweep")
+        return {k: v for k, v in _struct_dict(s).items() if k != "reserved"}
 
     def tune(self, max_steps: int):
         """Times launch shapes on the live state (advancing it) and keeps the fastest; returns

@@ -180,7 +180,7 @@ struct btrt3 {
     int64_t step = 0;
     int check_interval = 1000;
     int cus = 256;                          // compute units of the device
-    int mom_chunks[3] = {0, 0, 0};          // mom_chunk by steps per launch, once computed
+    mutable int mom_chunks[3] = {0, 0, 0};  // mom_chunk by steps per launch, once computed
     btrt3_launch_t launch{0, 0, 0};         // as set (0: automatic)
     Sweep3<double> a64{};
     Sweep3<float> a32{};
@@ -302,21 +302,49 @@ int setup(btrt3* h, const btrt3_flux_t* B, const btrt3_diff_t* K, const btrt3_so
 // up, else one (us a step with one and two: 74 x 58 x 46 FP64 8.9 and 9.8, FP32 6.4 and 7.9; 128 x 128
 // x 100 31.1 and 27.7, 19.7 and 18.0; 230 x 110 x 200 88.5 and 65.4; with Dirichlet faces, whose
 // bounce-back costs two steps more registers than there are, 118 and 380, 53.9 and 54.8).
-int mom_auto_steps(const btrt3* h)
+// The population form: two on periodic boxes from 2^21 nodes up, else one (with Dirichlet faces the bounced
+// links of two levels do not fit the registers: us a step with one and two, 160 x 150 x 140 FP64 206 and 609,
+// FP32 104 and 151; 256^3 1049 and 2997, 520 and 716; periodic 200 and 127, 104 and 73).
+int auto_steps(const btrt3* h)
 {
     const int* per = h->precision == BTRT_F64 ? h->a64.per : h->a32.per;
     const bool periodic = per[0] && per[1] && per[2];
-    return periodic && static_cast<int64_t>(h->nx) * h->ny * h->nz >= (int64_t(1) << 20) ? 2 : 1;
+    const int64_t nodes = static_cast<int64_t>(h->nx) * h->ny * h->nz;
+    return periodic && nodes >= (int64_t(1) << (h->mom ? 20 : 21)) ? 2 : 1;
+}
+
+// Planes per workgroup of a moment-form launch of `steps` steps: a workgroup walks its chunk plus
+// `steps` planes on each side, and the launch takes as many rounds of resident workgroups as it needs.
+int mom_chunk(const btrt3* h, int steps)
+{
+    if (h->mom_chunks[steps] > 0) return h->mom_chunks[steps];
+    const int per_cu = h->precision == BTRT_F64 ? mom3_blocks_per_cu<double>(h->a64, h->k1_per_node, steps)
+                                                : mom3_blocks_per_cu<float>(h->a32, h->k1_per_node, steps);
+    const int64_t slots = static_cast<int64_t>(h->cus) * per_cu;
+    int64_t best = -1;
+    int chunk = h->nz;
+    for (int zc = 1; zc <= 256; ++zc) {
+        const int use = std::min(zc, h->nz);
+        const int64_t cost = ((mom3_workgroups(h->nx, h->ny, h->nz, steps, use) + slots - 1) / slots) * (use + 2 * steps);
+        if (best < 0 || cost < best) {
+            best = cost;
+            chunk = use;
+        }
+        if (use == h->nz) break;
+    }
+    h->mom_chunks[steps] = chunk;
+    return chunk;
 }
 
 // Launch shape with the automatic fields resolved for the handle's grid.
 btrt3_launch_t resolve_launch(const btrt3* h)
 {
     btrt3_launch_t c = h->launch;
-    const int64_t nodes = static_cast<int64_t>(h->nx) * h->ny * h->nz;
-    if (c.steps_per_launch == 0) c.steps_per_launch = nodes >= (int64_t(1) << 21) ? 2 : 1;
+    if (c.steps_per_launch == 0) c.steps_per_launch = auto_steps(h);
     if (c.tile == 0) c.tile = 1;
-    if (c.z_chunk == 0) {
+    if (c.z_chunk == 0 && h->mom) {
+        c.z_chunk = mom_chunk(h, c.steps_per_launch);
+    } else if (c.z_chunk == 0) {
         // Workgroups run in rounds of (compute units x workgroups each holds); a workgroup walks its
         // chunk plus one plane on each side. Among chunks of 16 .. 64 planes take the one with the
         // fewest rounds x (chunk + 2) planes walked: the last round of a launch is then nearly
@@ -343,29 +371,6 @@ btrt3_launch_t resolve_launch(const btrt3* h)
     return c;
 }
 
-// Planes per workgroup of a moment-form launch of `steps` steps: a workgroup walks its chunk plus
-// `steps` planes on each side, and the launch takes as many rounds of resident workgroups as it needs.
-int mom_chunk(btrt3* h, int steps)
-{
-    if (h->mom_chunks[steps] > 0) return h->mom_chunks[steps];
-    const int per_cu = h->precision == BTRT_F64 ? mom3_blocks_per_cu<double>(h->a64, h->k1_per_node, steps)
-                                                : mom3_blocks_per_cu<float>(h->a32, h->k1_per_node, steps);
-    const int64_t slots = static_cast<int64_t>(h->cus) * per_cu;
-    int64_t best = -1;
-    int chunk = h->nz;
-    for (int zc = 1; zc <= 256; ++zc) {
-        const int use = std::min(zc, h->nz);
-        const int64_t cost = ((mom3_workgroups(h->nx, h->ny, h->nz, steps, use) + slots - 1) / slots) * (use + 2 * steps);
-        if (best < 0 || cost < best) {
-            best = cost;
-            chunk = use;
-        }
-        if (use == h->nz) break;
-    }
-    h->mom_chunks[steps] = chunk;
-    return chunk;
-}
-
 // n steps of a handle in the moment form.
 int mom_steps(btrt3* h, const btrt3_launch_t& c, int64_t n)
 {
@@ -375,10 +380,8 @@ int mom_steps(btrt3* h, const btrt3_launch_t& c, int64_t n)
     }
     if (n <= 0) return BTRT_OK;
     const int zc = h->launch.z_chunk;
-    int most = c.steps_per_launch;
-    if (h->launch.steps_per_launch == 0) most = mom_auto_steps(h);
     while (n > 0) {
-        const int k = static_cast<int>(std::min<int64_t>(most, n));
+        const int k = static_cast<int>(std::min<int64_t>(c.steps_per_launch, n));
         const int chunk = zc > 0 && c.steps_per_launch == 2 ? zc : mom_chunk(h, k);
         const hipError_t e = h->precision == BTRT_F64
                                  ? launch3_mom<double>(args<double>(h, h->cur), h->k1_per_node, k, chunk, h->stream)
@@ -509,14 +512,8 @@ int btrt3_step(btrt3_t* h, int64_t n)
         const int rc = mom_steps(h, c, n);
         return rc == BTRT_OK ? ok() : rc;
     }
-    // With Dirichlet faces the automatic shape runs one step per launch: the bounced links of two levels
-    // do not fit the registers (us a step with one and two: 160 x 150 x 140 FP64 206 and 609, FP32 104
-    // and 151; 256^3 1049 and 2997, 520 and 716; periodic 200 and 127, 104 and 73).
-    const int* per = h->precision == BTRT_F64 ? h->a64.per : h->a32.per;
-    const bool faces = !(per[0] && per[1] && per[2]);
-    const bool pairs = c.steps_per_launch == 2 && !(faces && h->launch.steps_per_launch == 0);
     for (int64_t s = 0; s < n;) {
-        const bool two = pairs && n - s >= 2;
+        const bool two = c.steps_per_launch == 2 && n - s >= 2;
         const bool f64 = h->precision == BTRT_F64;
         hipError_t e;
         if (two)
@@ -553,6 +550,7 @@ int btrt3_get_launch(const btrt3_t* h, btrt3_launch_t* cfg)
 {
     if (!h) return fail(BTRT_E_STATE, "NULL handle");
     if (!cfg) return fail(BTRT_E_INVAL, "cfg is NULL");
+    DeviceGuard g(h->device);
     *cfg = resolve_launch(h);
     return ok();
 }

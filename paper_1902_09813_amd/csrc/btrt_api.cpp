@@ -447,6 +447,15 @@ int btrt_get_launch(btrt_t* h, btrt_launch_t* cfg)
     return ok();
 }
 
+int btrt_get_sweep(btrt_t* h, btrt_sweep_t* sweep)
+{
+    if (!h) return fail(BTRT_E_STATE, "NULL handle");
+    if (!sweep) return fail(BTRT_E_INVAL, "sweep is NULL");
+    DeviceGuard g(h->device);
+    *sweep = instance_sweep(h->inst, h->launch);
+    return ok();
+}
+
 int btrt_tune(btrt_t* h, int64_t max_steps, btrt_launch_t* best, int64_t* steps_used)
 {
     if (!h) return fail(BTRT_E_STATE, "NULL handle");
@@ -511,7 +520,7 @@ int btrt_tune(btrt_t* h, int64_t max_steps, btrt_launch_t* best, int64_t* steps_
     // so pass 2 re-times the kFinal fastest and the automatic shape in turn, twice over, two timed
     // launches each, and keeps the lowest mean.
     constexpr int kFinal = 4;
-    const int64_t warm = std::min<int64_t>(max_steps / 10, 8LL * automatic.steps);
+    const int64_t warm = std::min<int64_t>(max_steps / 10, 8LL * (automatic.fuse > 0 ? automatic.fuse : automatic.steps));
     if (warm > 0) {
         int rc0 = enqueue_steps(h, automatic, warm);
         if (rc0 != BTRT_OK) return rc0;
@@ -536,7 +545,9 @@ int btrt_tune(btrt_t* h, int64_t max_steps, btrt_launch_t* best, int64_t* steps_
         const double ms = n2[c] > 0 ? t2[c] / n2[c] : t1[c];  // pass 1 only when the steps ran out
         if (best_ms < 0 || ms < best_ms) {
             best_ms = ms;
-            pick = cand[c];
+            // The automatic shape stays automatic: what it resolves to depends on the model in force, which a
+            // wall schedule changes.
+            pick = c == 0 ? LaunchCfg{} : cand[c];
         }
     }
     h->launch = pick;

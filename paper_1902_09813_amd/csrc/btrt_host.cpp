@@ -653,6 +653,35 @@ int instance_launch(Instance& I, const LaunchCfg& cfg, hipStream_t s)
     return BTRT_OK;
 }
 
+// The launch of a resolved shape that comes next when `left` steps are left.
+static LaunchCfg next_launch(const Instance& I, const LaunchCfg& c, int64_t left)
+{
+    LaunchCfg k = c;
+    k.steps = static_cast<int>(std::min<int64_t>(c.fuse > 0 ? c.fuse : c.steps, left));
+    if (I.mom && I.gen && k.block == 0) k.steps = k.steps >= 4 ? 4 : (k.steps >= 2 ? 2 : 1);  // the launches it has
+    if (k.steps != 2) k.tile = 0;
+    if (k.steps == 1 && c.steps != 1) k.rows = k.group = 0;  // the one-step kernel's own tiles
+    return k;
+}
+
+btrt_sweep_t instance_sweep(const Instance& I, const LaunchCfg& want)
+{
+    const LaunchCfg k = next_launch(I, instance_resolve(I, want), INT32_MAX);
+    const int es = I.precision == BTRT_F64 ? 8 : 4;
+    const SweepShape w = sweep_shape(k, I.mom, es);
+    btrt_sweep_t s{};
+    s.kernel = w.kernel;
+    s.steps_per_launch = k.steps;
+    s.columns = w.columns;
+    s.rows = w.rows;
+    s.threads = w.threads;
+    s.moments = I.mom ? 1 : 0;
+    s.automatic = want.steps <= 0 ? 1 : 0;
+    s.bytes_per_node = 2.0 * (I.state_planes() * static_cast<double>(I.state_bytes()) + es) +
+                       ((I.kind == kSrcField ? 1 : 0) + (I.afield ? 3 : 0)) * es;
+    return s;
+}
+
 int instance_steps(Instance& I, const LaunchCfg& want, int64_t n, hipStream_t s)
 {
     if (n <= 0) return BTRT_OK;
@@ -664,13 +693,8 @@ int instance_steps(Instance& I, const LaunchCfg& want, int64_t n, hipStream_t s)
         --n;
     }
     const LaunchCfg c = instance_resolve(I, want);
-    const int per = c.fuse > 0 ? c.fuse : c.steps;
     for (int64_t i = 0; i < n;) {
-        LaunchCfg k = c;
-        k.steps = static_cast<int>(std::min<int64_t>(per, n - i));
-        if (I.mom && I.gen && k.block == 0) k.steps = k.steps >= 4 ? 4 : (k.steps >= 2 ? 2 : 1);  // the launches it has
-        if (k.steps != 2) k.tile = 0;
-        if (k.steps == 1 && c.steps != 1) k.rows = k.group = 0;  // the one-step kernel's own tiles
+        const LaunchCfg k = next_launch(I, c, n - i);
         int rc = instance_launch(I, k, s);
         if (rc != BTRT_OK) return rc;
         i += k.steps;

@@ -148,6 +148,8 @@ int instance_launch(Instance& I, const btrtk::LaunchCfg& cfg, hipStream_t s);
 int instance_steps(Instance& I, const btrtk::LaunchCfg& want, int64_t n, hipStream_t s);
 // cfg with its automatic fields resolved for I's grid and format on the current device.
 btrtk::LaunchCfg instance_resolve(const Instance& I, const btrtk::LaunchCfg& cfg);
+// What a launch of btrt_step runs with that shape wanted.
+btrt_sweep_t instance_sweep(const Instance& I, const btrtk::LaunchCfg& want);
 // Enqueues the two-pass reduction (residual or error) into I's result slot (no sync).
 int instance_reduce_async(Instance& I, int mode, hipStream_t s);
 // Copies device memory to a host array; returns when complete.

@@ -166,6 +166,12 @@ template <typename T>
 hipError_t launch_batch_mom(const BatchEntry<T>* ent, const int* begin, const int* par, int ninst, int total, int flip,
                             int steps, int grid, int rows, hipStream_t s);
 int mom_strip_columns(int steps);
+// What one launch of a single handle covers: the nodes a unit of its grid of workgroups writes (a tile, a strip
+// or a region; less at the far edges) and the threads of a workgroup. cfg: as a launch takes it, all resolved.
+struct SweepShape {
+    int kernel, columns, rows, threads;  // kernel: BTRT_SWEEP_*
+};
+SweepShape sweep_shape(const LaunchCfg& cfg, bool mom, int value_bytes);
 // f+(0) of the moment form into both buffers of a handle (a: the arguments of parity 1; ab and cq as for
 // launch_init).
 template <typename T>

@@ -4,6 +4,8 @@
 
 #include "btrt_mom.h"
 
+#include "btrt.h"
+
 namespace btrtk {
 namespace {
 
@@ -353,6 +355,20 @@ hipError_t launch_init(const SweepArgs<T>& a, int fmt, const double* phi0, const
                        const double cq[3], const double dq[4], hipStream_t s)
 {
     BTRT_BY_FORMAT(T, init_with, a, phi0, wall, ab, cq, dq, s);
+}
+
+SweepShape sweep_shape(const LaunchCfg& c, bool mom, int value_bytes)
+{
+    if (c.block > 0 && c.steps > 1) {
+        if (c.wrows > 0) return {BTRT_SWEEP_REGIONS, kWave - 2 * c.steps, c.block / kWave * c.wrows - 2 * c.steps, c.block};
+        const int log_ex = block_log_ex(c.block), halo = mom ? c.steps : c.steps - 1;
+        return {BTRT_SWEEP_BLOCKS, (1 << log_ex) - 2 * halo, (c.block >> log_ex) - 2 * halo, c.block};
+    }
+    if (c.steps == 1) return {BTRT_SWEEP_STEP, kTileX, c.rows, kTileX * c.rows};
+    if (c.tile && !mom) return {BTRT_SWEEP_TILE, kTile2X, tile_rows(2, value_bytes), kBlock2};
+    const int columns = mom ? kWave * mom_walk_columns(value_bytes, c.steps) - 2 * c.steps : batch_strip_columns(c.steps);
+    const int rows = mom && c.fit_rows > 0 ? c.fit_rows : (c.rows > 0 ? c.rows : tile_rows(2, value_bytes));
+    return {BTRT_SWEEP_STRIPS, columns, rows, kWave * (c.group == kWalkGroup ? kWalkGroup : 1)};
 }
 
 template <typename T>

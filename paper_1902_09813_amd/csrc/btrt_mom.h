@@ -792,8 +792,9 @@ hipError_t mom_one_launch(SweepArgs<T> a, int rows, hipStream_t s)
 // the halo is 12 or 14 of 128 columns instead of 64: 4096^2, seven steps, 27.3 us a step against
 // 32.9; FP64, whose six- and seven-step walkers would leave one wavefront per SIMD, 47.3 against
 // 47.9 us at five steps, so it keeps one column).
+constexpr int mom_walk_columns(int value_bytes, int steps) { return value_bytes == 4 && steps >= 6 ? 2 : 1; }
 template <typename T, int K>
-constexpr int mom_columns() { return sizeof(T) == 4 && K >= 6 ? 2 : 1; }
+constexpr int mom_columns() { return mom_walk_columns(sizeof(T), K); }
 
 // Resident wavefronts per SIMD of one walker instantiation.
 template <typename T, bool SRC, int KM, int K, bool WALLS>

@@ -1,6 +1,6 @@
 /* A stand-in for the HIP runtime calls libbtrt.so makes, for tests of its host code without a GPU: device
- * memory is host memory, copies happen at once, kernels do nothing. A test can make a copy fail and ask which
- * threads launched on a stream. */
+ * memory is host memory, copies happen at once, kernels do nothing and take a millisecond each of the time events tell. A test
+ * can make a copy fail and ask how many launches, of which threads, a stream got. */
 #define __HIP_PLATFORM_AMD__ 1
 #include <hip/hip_runtime_api.h>
 
@@ -70,19 +70,36 @@ hipError_t hipMemcpyAsync(void* dst, const void* src, size_t n, hipMemcpyKind k,
 }
 
 static char handles[64];
+static atomic_long launched; /* launches so far: the clock of events */
+static long stamp[64];
 hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned f) { (void)f; *s = (hipStream_t)&handles[0]; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { (void)s; return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t s) { (void)s; return hipSuccess; }
-hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)&handles[1]; return hipSuccess; }
+static atomic_int events;
+hipError_t hipEventCreate(hipEvent_t* e)
+{
+    *e = (hipEvent_t)&stamp[atomic_fetch_add(&events, 1) % 64];
+    return hipSuccess;
+}
 hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned f) { (void)f; return hipEventCreate(e); }
 hipError_t hipEventDestroy(hipEvent_t e) { (void)e; return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { (void)e; (void)s; return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s)
+{
+    (void)s;
+    *(long*)e = atomic_load(&launched);
+    return hipSuccess;
+}
 hipError_t hipEventSynchronize(hipEvent_t e) { (void)e; return hipSuccess; }
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) { (void)a; (void)b; *ms = 1.0f; return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b)
+{
+    *ms = (float)(*(long*)b - *(long*)a); /* a millisecond a launch */
+    return hipSuccess;
+}
 
 hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t lds, hipStream_t s)
 {
     (void)f; (void)grid; (void)block; (void)args; (void)lds;
+    atomic_fetch_add(&launched, 1);
     if (s == watched) {
         atomic_fetch_add(&total, 1);
         if (!pthread_equal(pthread_self(), owner)) atomic_fetch_add(&foreign, 1);

@@ -29,32 +29,43 @@ def test_sweep_launch_count():
     assert bench.sweep_launches(0, 7) == 0
 
 
+def _sweep(kernel, k, columns, rows, words, value=8):
+    return dict(kernel=kernel, steps_per_launch=k, columns=columns, rows=rows, threads=64, moments=int(words < 10),
+                automatic=1, bytes_per_node=2.0 * words * value)
+
+
 def test_traffic_record_lookup():
     with open(bench.TRAFFIC_FILE) as fh:
         rec = json.load(fh)
     nodes = 4096 * 4096
     if rec["kernel_sha256_16"] != bench.kernel_hash():
         # Counters taken on other kernel sources: the benchmark must report no traffic.
-        assert bench.traffic_for("f64", nodes, dict(steps_per_launch=7, strip_rows=342, strips_per_group=1,
-                                                    tile=0)) is None
+        for key in (k for k in rec if k.startswith("f64_")):
+            kernel, _, rest = key[4:].rpartition("_k")
+            k, shape = rest.split("_")[:2]
+            if "x" in shape:
+                columns, rows = (int(v) for v in shape.split("x"))
+                assert bench.traffic_for("f64", nodes, _sweep(kernel, int(k), columns, rows, 3)) is None
         pytest.skip("the HBM counter record predates the current kernel sources")
-    # The tuned shape of the FP64 workload: seven steps, strips tall enough for one round.
-    shape = dict(steps_per_launch=7, strip_rows=342, strips_per_group=1, tile=0)
+    keys = [k for k in rec if k.startswith("f64_mom_walk_kernel_k7_50x")]
+    assert len(keys) == 1  # the FP64 workload's automatic shape: seven steps, strips for one round
+    shape = _sweep("mom_walk_kernel", 7, 50, int(keys[0].rsplit("x", 1)[1]), 3)
+    assert bench.traffic_key("f64", shape) == keys[0]
     got = bench.traffic_for("f64", nodes, shape)
-    alg = 160 * nodes
-    assert got is not None and alg <= got <= 1.3 * alg
+    alg = 48 * nodes  # phi and two moments, read and written once
+    assert got is not None and alg <= got <= 1.5 * alg
     busy = bench.valu_busy_for("f64", nodes, shape)
     assert busy is not None and 0.0 < busy <= 1.0
-    assert bench.valu_busy_for("f64", nodes, dict(shape, strip_rows=8)) is None
+    assert bench.valu_busy_for("f64", nodes, dict(shape, rows=8)) is None
     assert bench.traffic_for("f64", nodes + 1, shape) is None  # another grid
-    assert bench.traffic_for("f64", nodes, dict(shape, strip_rows=8)) is None  # a shape not measured
-    assert bench.traffic_key("f32", dict(steps_per_launch=4, strip_rows=32, strips_per_group=4, tile=0)) == \
-        "f32_k4_r32_g4_t0"
+    assert bench.traffic_for("f64", nodes, dict(shape, rows=8)) is None  # a shape not measured
+    assert bench.traffic_for("f64", nodes, dict(shape, kernel="walk_kernel")) is None  # another kernel
 
 
-def _run(k, us, nodes=4096 * 4096, tile=0):
-    return {"launch": dict(steps_per_launch=k, strip_rows=64, strips_per_group=1, tile=tile), "launch_ms_avg": us * 1e-3,
-            "nodes": nodes, "bytes_per_node_launch": 160.0}
+def _run(k, us, nodes=4096 * 4096):
+    return {"launch": dict(steps_per_launch=k, strip_rows=64, strips_per_group=1, tile=0), "launch_ms_avg": us * 1e-3,
+            "sweep": _sweep("sweep_kernel" if k == 1 else "walk_kernel", k, 52, 64, 10), "nodes": nodes,
+            "bytes_per_node_launch": 160.0}
 
 
 def test_roofline_bound_follows_the_launch_shape():
@@ -75,12 +86,12 @@ def test_roofline_bound_follows_the_launch_shape():
     # shape when it covers it (the measured seven-step shape, on the current sources), else the
     # per-launch HBM view.
     r32 = bench.roofline_of(_run(7, 400.0), "f32")
-    lanes = bench.valu_lanes_for("f32", 4096 * 4096, r32["launch"])
+    lanes = bench.valu_lanes_for("f32", 4096 * 4096, r32["sweep"])
     if lanes is None:
         assert r32["bound"] == "hbm"
     else:
         assert r32["bound"] == "alu" and r32["unit"] == "T lane-instructions/s" and r32["peak"] == 39.3
         assert r32["achieved"] == pytest.approx(lanes * 7 * 4096 * 4096 / 400e-6 / 1e12, rel=1e-3)
     unmeasured = _run(7, 400.0)
-    unmeasured["launch"]["strip_rows"] = 8
+    unmeasured["sweep"]["rows"] = 8
     assert bench.roofline_of(unmeasured, "f32")["bound"] == "hbm"

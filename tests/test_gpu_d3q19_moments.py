@@ -3,6 +3,7 @@ bit for bit between one and two steps per launch and chunk heights, around the t
 output columns with one step per launch, 60 x 12 with two), for boxes thinner than a tile, on every
 kind of boundary (edges and corners of the box with unequal face values), with and without a source.
 """
+import dataclasses
 import sys
 
 import numpy as np
@@ -87,3 +88,21 @@ def test_determinant_beyond_the_range(precision, scale, tol):
             s.set_launch(*shape)
             phi = s.step(w.steps).field()
         assert normwise(phi, want) <= tol, shape
+
+
+def test_reported_shape_is_the_one_that_runs():
+    # A shape read from one handle and set on another is the shape the first one runs: two steps per launch
+    # only where the automatic choice takes them.
+    for w, k in [(W.d3_nonlinear(104, 104, 100, steps=5), 2), (W.d3_nonlinear(60, 60, 60, steps=5), 1),
+                 (box(128, 128, 128, (1,) * 6, False, 0.0), 1), (dataclasses.replace(box(128, 128, 128, (0, 0, 1, 1, 0, 0),
+                                                                                   False, 0.0), k2=1.1), 1),
+                 (dataclasses.replace(W.d3_nonlinear(128, 128, 128, steps=5), k2=1.1), 2),
+                 (dataclasses.replace(W.d3_nonlinear(104, 104, 100, steps=5), k2=1.1), 1)]:
+        with btrt3.Solver3(btrt3.problem_from_workload3(w), w.phi0()) as s:
+            shape = s.launch()
+            assert shape[0] == k, (w.name, shape)
+            want = s.step(5).populations()
+        with btrt3.Solver3(btrt3.problem_from_workload3(w), w.phi0()) as s:
+            s.set_launch(*shape)
+            assert s.launch() == shape
+            assert np.array_equal(s.step(5).populations(), want)

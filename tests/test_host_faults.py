@@ -108,3 +108,70 @@ with solver() as s, solver() as ref:
             raise AssertionError("stepped past the schedule")
 print("done")
 """)
+
+
+def test_reported_sweeps_are_the_launches_made(fake_lib):
+    # btrt_get_sweep against the launches a stream gets: k launches for k times its steps, one more for a step
+    # more (or for what the general model's walkers make of the rest), for every form, storage and model.
+    run(fake_lib, """
+S = 0x1000
+kinds = set()
+for n in (16, 64, 200, 330, 500, 1100):
+    for precision in (btrt.F64, btrt.F32, btrt.F16DEV):
+        for kw in (dict(), dict(k2=1.1), dict(bc_type=(1,) * 4), dict(bc_type=(1,) * 4, k2=0.9), dict(beta=0.3),
+                   dict(flux_c=(0.01, 0.0), flux_q=2.0), dict(flux_c=(0.01, 0.0), flux_q=2.0, k2=1.1)):
+            if "flux_c" in kw and precision == btrt.F16DEV:
+                continue
+            p = btrt.Problem(n, n, A0=(0.01, 0.0, 0.01), precision=precision, **kw)
+            p.grid.stream = S
+            with btrt.Solver(p, np.zeros((n, n))) as s:
+                s.step(1)
+                for shape in ((0, 0, 0, 0), (1, 0, 0, 0), (2, 0, 0, 1), (4, 0, 0, 0), (4, 16, 4, 0), (6, 0, 0, 0), (7, 32, 1, 0)):
+                    w = s.set_launch(*shape).sweep()
+                    k = w["steps_per_launch"]
+                    kinds.add((w["kernel"], w["moments"]))
+                    fake.fake_watch(S)
+                    s.step(5 * k)
+                    assert fake.fake_launches() == 5, (n, precision, kw, shape, w, fake.fake_launches())
+                    s.step(k + 1)
+                    assert fake.fake_launches() == 7, (n, precision, kw, shape, w, fake.fake_launches())
+                    assert w["automatic"] == (shape[0] == 0) and w["columns"] > 0 and w["rows"] > 0
+                    assert w["moments"] == ("k2" not in kw)
+                    if shape[0] == 1:
+                        assert (w["kernel"], w["columns"], w["rows"], w["threads"]) == (btrt.SWEEP_STEP, 64, 4, 256)
+                    if shape == (4, 16, 4, 0):
+                        assert (w["kernel"], w["rows"], w["threads"]) == (btrt.SWEEP_STRIPS, 16, 256)
+                    words = 3 if w["moments"] else 10
+                    if precision != btrt.F16DEV:
+                        assert w["bytes_per_node"] == 2 * words * (8 if precision == btrt.F64 else 4)
+assert kinds == {(btrt.SWEEP_STEP, 0), (btrt.SWEEP_STEP, 1), (btrt.SWEEP_TILE, 0), (btrt.SWEEP_STRIPS, 0),
+                 (btrt.SWEEP_STRIPS, 1), (btrt.SWEEP_BLOCKS, 0), (btrt.SWEEP_BLOCKS, 1), (btrt.SWEEP_REGIONS, 1)}, kinds
+print("done")
+""")
+
+
+def test_a_tuned_shape_runs_on_another_handle_and_follows_the_model(fake_lib):
+    # What btrt_tune keeps, set elsewhere as btrt_get_sweep says to, runs the same launches; and an automatic
+    # choice is made again when a wall schedule changes the model.
+    run(fake_lib, """
+seen = set()
+for n in (20, 64, 100, 330, 500, 1100):
+    for kw, budget in ((dict(), 2000), (dict(), 30), (dict(k2=1.1), 2000), (dict(k2=1.1), 30)):
+        make = lambda: btrt.Solver(btrt.Problem(n, n, A0=(0.01, 0.0, 0.01), bc_type=(1,) * 4, **kw), np.zeros((n, n)))
+        walls = np.zeros((40, 8 * n + 4))
+        with make() as a, make() as b:
+            best, used = a.tune(budget)  # with few steps only the automatic shape and its like are timed
+            assert used > 0 and best == a.launch()
+            w = a.sweep()
+            seen.add(w["automatic"])
+            b.set_launch(*((0, 0, 0, 0) if w["automatic"] else best))
+            assert b.sweep() == w, (n, kw, w, b.sweep())
+            for s in (a, b):
+                s.set_walls(walls)
+            assert a.sweep() == b.sweep(), (n, kw, a.sweep(), b.sweep())
+            if w["automatic"]:
+                with make() as c:
+                    assert c.set_walls(walls).sweep() == a.sweep(), (n, kw)
+assert seen == {0, 1}, seen
+print("done")
+""")
