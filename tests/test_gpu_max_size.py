@@ -6,7 +6,8 @@ phi0 repeats a seeded 64 x 64 pattern, so on a periodic grid the exact solution 
 64 x 64 tile of the GPU field must equal the first one bit for bit (which checks the indexing over
 the whole grid), and the first tile must match the FP64 oracle run on the 64 x 64 pattern, within
 the storage format's bound. Six steps run in one six-step walker launch and one more in the one-step
-kernel; mass is conserved."""
+kernel; mass is conserved. Each storage with K2 = 1, where the state is moments, and with other rates, where it
+is the nine populations (the planes and the index range the library's limit is set for)."""
 import sys
 
 import numpy as np
@@ -33,15 +34,16 @@ def pattern():
     return 0.5 + 0.25 * np.sin(2 * np.pi * X) * np.cos(4 * np.pi * Y) + 0.15 * np.cos(2 * np.pi * (X + 2 * Y))
 
 
-def workload(n):
+def workload(n, k2):
     return W.Workload(f"max_{n}", n, n, 7, flux_b=(0.025, 0.025), flux_a=(0.01, -0.01), A0=(0.01, 0.0, 0.005),
-                      beta=1.0)
+                      beta=1.0, k2=k2)
 
 
+@pytest.mark.parametrize("k2", [1.0, (1.1, 0.9, 0.9, 1.2)], ids=["moments", "populations"])
 @pytest.mark.parametrize("n,precision,bound", [(46336, btrt.F32, 5e-5), (46336, btrt.F16DEV, 1e-4),
                                                (32768, btrt.F64, 1e-12)], ids=["f32_46336", "f16dev_46336", "f64_32768"])
-def test_largest_grid(n, precision, bound):
-    w = workload(n)
+def test_largest_grid(n, precision, bound, k2):
+    w = workload(n, k2)
     say(f"[gpu] max size {n}x{n} precision {precision}")
     p = btrt.problem_from_workload(w, precision=precision)
     assert p.validate().pitch == n
@@ -62,7 +64,7 @@ def test_largest_grid(n, precision, bound):
     assert np.array_equal(phi[:, :P].reshape(n // P, P, P), np.broadcast_to(first, (n // P, P, P)))
     m1 = float(np.sum(phi, dtype=np.float64))
     del phi
-    small = W.Workload("max_tile", P, P, 7, flux_b=w.flux_b, flux_a=w.flux_a, A0=w.A0, beta=w.beta)
+    small = W.Workload("max_tile", P, P, 7, flux_b=w.flux_b, flux_a=w.flux_a, A0=w.A0, beta=w.beta, k2=k2)
     o = O.Oracle(oracle_problem(small), pattern(), nthreads=0).step(7)
     e = normwise(first, o.phi())
     say(f"    first tile vs oracle normwise {e:.3e}; mass drift {abs(m1 - m0) / m0:.2e}")
