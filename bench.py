@@ -16,6 +16,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -54,11 +55,12 @@ SWEEP_KERNELS = (("sweep_kernel", "mom_sweep_kernel"), ("sweep2_kernel", None), 
 
 
 def kernel_hash() -> str:
-    """sha256 (first 16 hex digits) over the device-code sources, in a fixed order."""
+    """sha256 (first 16 hex digits) over the device-code sources, in a fixed order, comments and layout
+    left out."""
     h = hashlib.sha256()
     for name in KERNEL_SOURCES:
-        with open(os.path.join(CSRC, name), "rb") as fh:
-            h.update(fh.read())
+        with open(os.path.join(CSRC, name)) as fh:
+            h.update(" ".join(re.sub(r"//[^\n]*", "", fh.read()).split()).encode())
     return h.hexdigest()[:16]
 
 
