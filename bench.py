@@ -28,9 +28,10 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 # MI355X FP64 vector peak: 256 CUs x 4 SIMDs x 16 FP64 lanes x 2 flops (FMA) x 2.4 GHz.
 FP64_PEAK_TFLOPS = 78.6
-# VALU lane-instruction issue peak: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz (every FP64 VALU
-# instruction of a 64-wide wavefront occupies its SIMD for four cycles, and so does every FP32 or
-# 16-bit one that is not packed).
+# VALU lane-instruction issue peak: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz: an FP64 VALU instruction of a
+# 64-wide wavefront occupies its SIMD for four cycles, and so does an FP32 one that is not packed (a loop of
+# them: 38 T; with several wavefronts a SIMD, lane shifts and other instructions can go beside one, so a
+# kernel's count of all its VALU instructions may pass this rate, its arithmetic not).
 FP64_ISSUE_PEAK_T = 39.3
 # One node update of the 4096^2 nonlinear workload (k0 = K2 = 1, K1 per node, Burgers flux, no source)
 # as the moment form's pull and collision are written: FP64 flops (an FMA counts two) and FP64 VALU
@@ -445,11 +446,12 @@ def roofline_of(r, precision_name):
     """Roofline of the timed sweep kernel. One step per launch moves the whole state every step
     and is bound by HBM: achieved = algorithmic bytes per launch / launch time against 8 TB/s. A
     launch that fuses K steps reads and writes the state once for K node updates per node, so its
-    bytes per update fall by K and the arithmetic becomes the limit. FP64 storage: achieved = FP64
-    flops of the K updates / launch time against the FP64 vector peak. FP32 and 16-bit storage
-    (FP32 arithmetic, issued at the FP64 rate when not packed): achieved = the VALU lane-
-    instructions the counter record measured for the shape / launch time against the issue peak
-    (HBM as the bound when no record covers the shape). The HBM figures stand beside it."""
+    bytes per update fall by K and the arithmetic becomes the limit. FP64 storage, and the moment
+    form in every storage (FP32 arithmetic issues at the FP64 rate when not packed): achieved =
+    flops of the K updates / launch time against the FP64 vector peak. FP32 and 16-bit
+    populations: achieved = the VALU lane-instructions the counter record measured for the shape
+    / launch time against the issue peak (HBM as the bound when no record covers the shape). The
+    HBM figures stand beside it."""
     sweep = r["sweep"]
     k = sweep["steps_per_launch"]
     t = r["launch_ms_avg"] * 1e-3
@@ -467,14 +469,15 @@ def roofline_of(r, precision_name):
                            "frac": round(hbm_launch / HBM_PEAK_GBS, 4), "bytes_per_launch": bytes_per_launch},
     }
     updates = nodes * k
-    lanes = valu_lanes_for(precision_name, nodes, sweep) if k > 1 and precision_name != "f64" else None
+    flops = k > 1 and (precision_name == "f64" or sweep["moments"])
+    lanes = valu_lanes_for(precision_name, nodes, sweep) if k > 1 and not flops else None
     if lanes is not None:
         issue = lanes * updates / t / 1e12
         out.update({"bound": "alu", "achieved": round(issue, 2), "peak": FP64_ISSUE_PEAK_T,
                     "unit": "T lane-instructions/s", "frac": round(issue / FP64_ISSUE_PEAK_T, 4),
                     "valu_lane_instructions_per_update": lanes})
         return out
-    if k == 1 or precision_name != "f64":
+    if not flops:
         out.update({"bound": "hbm", "achieved": round(hbm_launch, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": round(hbm_launch / HBM_PEAK_GBS, 4)})
         return out
@@ -487,11 +490,12 @@ def roofline_of(r, precision_name):
         "unit": "TFLOP/s",
         "frac": round(tflops / FP64_PEAK_TFLOPS, 4),
         "flops_per_update": FLOPS_PER_UPDATE,
-        "fp64_issue": {"instructions_per_update": FP64_INSTRUCTIONS_PER_UPDATE, "achieved": round(issue, 2),
-                       "peak": FP64_ISSUE_PEAK_T, "unit": "T lane-instructions/s",
-                       "frac": round(issue / FP64_ISSUE_PEAK_T, 4)},
-        "per_update_vs_one_step_hbm_roofline": round(BYTES_PER_UPDATE_F64 * updates / t / 1e9 / HBM_PEAK_GBS, 3),
+        "fp64_issue" if precision_name == "f64" else "fp32_issue": {
+            "instructions_per_update": FP64_INSTRUCTIONS_PER_UPDATE, "achieved": round(issue, 2),
+            "peak": FP64_ISSUE_PEAK_T, "unit": "T lane-instructions/s", "frac": round(issue / FP64_ISSUE_PEAK_T, 4)},
     })
+    if precision_name == "f64":
+        out["per_update_vs_one_step_hbm_roofline"] = round(BYTES_PER_UPDATE_F64 * updates / t / 1e9 / HBM_PEAK_GBS, 3)
     return out
 
 

@@ -82,7 +82,16 @@ def test_roofline_bound_follows_the_launch_shape():
     assert r7["achieved"] == pytest.approx(flops, rel=1e-3)
     assert 0 < r7["frac"] < 1 and 0 < r7["fp64_issue"]["frac"] < 1 and 0 < r7["hbm_per_launch"]["frac"] < 1
     assert r7["per_update_vs_one_step_hbm_roofline"] == pytest.approx(160 * 7 * 4096 * 4096 / 700e-6 / 8e12, rel=1e-3)
-    # FP32 storage: the VALU issue of the lane-instructions the counter record counted for the
+    # The moment form in FP32 (and in 16-bit handles): the same flops and instructions per update, unpacked at
+    # the FP64 rate, over the launches that run.
+    m32 = _run(7, 222.0)
+    m32.update(sweep=_sweep("mom_region_kernel", 7, 50, 82, 3, 4), bytes_per_node_launch=24.0)
+    m32 = bench.roofline_of(m32, "f32")
+    assert m32["kernel"] == "mom_region_kernel" and m32["bound"] == "alu" and m32["unit"] == "TFLOP/s"
+    assert m32["achieved"] == pytest.approx(bench.FLOPS_PER_UPDATE * 7 * 4096 * 4096 / 222e-6 / 1e12, rel=1e-3)
+    assert 0 < m32["frac"] < 1 and 0 < m32["fp32_issue"]["frac"] < 1
+    assert m32["hbm_per_launch"]["achieved"] == pytest.approx(24 * 4096 * 4096 / 222e-6 / 1e9, rel=1e-3)
+    # FP32 populations: the VALU issue of the lane-instructions the counter record counted for the
     # shape when it covers it (the measured seven-step shape, on the current sources), else the
     # per-launch HBM view.
     r32 = bench.roofline_of(_run(7, 400.0), "f32")
