@@ -32,7 +32,10 @@ def compare(w, precision, steps, walls=None):
                 s.set_walls(walls)
             s.set_launch(*shape)
             if shape[0] == 0:
-                assert s.launch() == (1, 4, 0, 0)
+                assert s.launch() == (1, 4, 0, 0)  # the nearest the public shapes have
+                sweep = s.sweep()
+                assert sweep["kernel"] == btrt.SWEEP_BLOCKS and sweep["steps_per_launch"] > 1
+                assert sweep["moments"] == (w.k0 == 1.0 and w.k2 == 1.0)
             s.step(steps - 4).step(4)
             out.append((s.populations(), s.field()))
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1]), (w.name, precision)

@@ -92,6 +92,25 @@ def test_initial_state_is_rounded_once(precision, u):
             assert np.all(np.abs(f[i] - feq) <= bound), (i, kw, precision)
 
 
+@pytest.mark.parametrize("size", [(97, 83), (400, 320)], ids=["blocks", "regions"])
+def test_periodic_shift_invariance(size):
+    # A run from a shifted field (and source) gives the shifted populations: no kernel mixes a node's data with
+    # its place in a tile, strip, block or region.
+    nx, ny = size
+    shift = (17, 40)
+    S = 1e-4 * np.random.default_rng(21).standard_normal((ny, nx))
+    w = dataclasses.replace(W.c3().scaled(nx, ny, 29), source=("field", S, 0.0))
+    ws = dataclasses.replace(w, source=("field", np.roll(S, shift, axis=(0, 1)), 0.0))
+    phi0 = w.phi0()
+    for precision in (btrt.F64, btrt.F32):
+        for launch in [(0, 0, 0, 0), (1, 4, 0, 0), (3, 8, 1, 0), (4, 16, 4, 0), (7, 32, 1, 0)]:
+            with btrt.Solver(btrt.problem_from_workload(w, precision=precision), phi0) as a, \
+                    btrt.Solver(btrt.problem_from_workload(ws, precision=precision), np.roll(phi0, shift, axis=(0, 1))) as b:
+                fa = a.set_launch(*launch).step(w.steps).populations()
+                fb = b.set_launch(*launch).step(w.steps).populations()
+            assert np.array_equal(np.roll(fa, shift, axis=(1, 2)), fb), (launch, precision)
+
+
 def test_determinant_beyond_the_range_of_fp32():
     # K1 = adj(M) / det M per node: det M overflows FP32 (3e38) while M does not, and 1/det M is then 0 as a
     # division gives it (K1 itself is below 1e-19), not NaN.

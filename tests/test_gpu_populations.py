@@ -9,7 +9,8 @@ workloads' sizes, with the rates K2 = (1.1, 0.9, 0.9, 1.2) in their place:
   every step count per launch, persistent and replayed from graphs, against each instance alone;
 * FP32 populations and the 16-bit encodings within stated bounds of the oracle, and the full 4096^2 and 1024^2
   workloads against the stored oracle results (FP64) and within the bounds stated for the formats there;
-* the two-step D3Q19 population kernel at its automatic shape.
+* checkpoints, wall schedules set on a plain problem, a caller's memory and stream beyond the cache;
+* the two-step D3Q19 population kernel at its automatic shape, and a cyclic shift of its periodic box.
 """
 import dataclasses
 import sys
@@ -206,3 +207,61 @@ def test_two_step_d3q19_populations_at_the_automatic_shape(bc):
             f = s.step(w.steps).populations()
         want = f if want is None else want
         assert np.array_equal(f, want), shape
+
+
+@pytest.mark.parametrize("precision", [btrt.F64, btrt.F32] + FORMATS, ids=lambda p: NAMES[p])
+def test_checkpoints_resume_bitwise(precision):
+    w = W.Workload("ck_rates", 131, 70, 0, A0=(0.03, 0.006, 0.02), beta=0.5, flux_a=(0.03, -0.02), flux_b=(0.02, 0.0),
+                   source=("sin", 2e-3, 1, 1), bc_type=(1, 1, 1, 1), bc_value=(0.2, 0.6, 0.4, 0.1), seed=21, k2=RATES)
+    for n1 in (0, 37):
+        with solver(w, precision) as a, solver(w, precision) as b, solver(w, precision) as ref:
+            r = [s.set_launch(4, 16, 4, 0).step(n1).residual() for s in (a, ref)]
+            b.set_launch(6, 32, 1, 0).restore(a.checkpoint())
+            assert r[0] == r[1] and b.info().step == n1
+            want = ref.step(53).populations()
+            assert np.array_equal(b.step(53).populations(), want) and b.residual() == ref.residual()
+    with solver(dataclasses.replace(w, k2=1.0), precision) as m, solver(w, precision) as p:  # the other form's state
+        for x, y in ((m, p), (p, m)):
+            with pytest.raises(btrt.BtrtError) as e:
+                x.restore(y.checkpoint())
+            assert e.value.code == btrt.E_INVAL
+
+
+@pytest.mark.parametrize("precision", [btrt.F64, btrt.F32], ids=lambda p: NAMES[p])
+def test_wall_schedules_on_a_plain_problem(precision):
+    # A schedule turns a plain population problem to the general node model; split, resumed and in every shape.
+    w = W.Workload("walls_table", 140, 90, 0, A0=(0.03, 0.0, 0.02), flux_a=(0.02, 0.01), bc_type=(1, 1, 0, 0),
+                   bc_value=(0.1, 0.2, 0.0, 0.0), seed=3, k2=RATES)
+    rows = np.random.default_rng(1).uniform(0.0, 1.0, (30, 4 * (140 + 90) + 4))
+    w.walls = lambda k: rows[k]
+    o = run_oracle(w, 30)
+    want = None
+    for shape in [(1, 0, 0, 0), (0, 0, 0, 0), (2, 0, 0, 1), (4, 16, 1, 0), (7, 8, 1, 0)]:
+        with solver(w, precision) as s:
+            s.set_launch(*shape).set_walls(rows[:12]).step(12)
+            data = s.checkpoint()
+        with solver(w, precision) as s:
+            f = s.set_launch(*shape).restore(data).set_walls(rows[12:]).step(18).populations()
+        if want is None:
+            want = f
+            if precision == btrt.F64:
+                assert normwise(f, o.f) <= 1e-12
+        assert np.array_equal(f, want), shape
+
+
+def test_callers_memory_and_stream_beyond_the_cache():
+    w = with_rates(W.c2().scaled(1400, 1300, 41))
+    with solver(w) as a, solver(w, torch_memory=True) as b:
+        assert np.array_equal(a.step(w.steps).field(), b.step(w.steps).field())
+
+
+def test_shift_invariance_d3q19_populations():
+    w = dataclasses.replace(W.d3_nonlinear(24, 19, 13, steps=9), k2=1.1)
+    shift = (5, 11, 7)
+    ws = dataclasses.replace(w, phi0_array=np.roll(w.phi0(), shift, axis=(0, 1, 2)))
+    for launch in [(1, 0, 0), (2, 3, 1), (2, 0, 3), (2, 5, 4)]:
+        with btrt3.Solver3(btrt3.problem_from_workload3(w), w.phi0()) as a, \
+                btrt3.Solver3(btrt3.problem_from_workload3(ws), ws.phi0()) as b:
+            fa = a.set_launch(*launch).step(w.steps).populations()
+            fb = b.set_launch(*launch).step(w.steps).populations()
+        assert np.array_equal(np.roll(fa, shift, axis=(1, 2, 3)), fb), launch

@@ -35,6 +35,7 @@ def _run(nx, ny, bc, kind, precision, launch):
     p = btrt.Problem(nx, ny, precision=precision, **kw)
     with btrt.Solver(p, rng.random((ny, nx))) as s:
         s.set_launch(*launch)
+        assert s.sweep()["kernel"] == (btrt.SWEEP_STEP if launch[0] else btrt.SWEEP_REGIONS)
         s.step(1).step(9).step(14)
         return s.field(), s.populations()
 
