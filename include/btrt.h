@@ -161,10 +161,10 @@ typedef struct {
     size_t workspace_bytes;           /* device bytes a handle needs */
     double bytes_per_node_launch;     /* algorithmic HBM bytes per node and sweep launch in the
                                          population form: the state read once and written once
-                                         (9 populations + phi each way; with k0 = 1 and K2 = 1 in
-                                         FP64/FP32 storage the library moves phi and two or three
-                                         moments instead) plus a source field and an A0 field when
-                                         given, however many steps the launch fuses */
+                                         (9 populations + phi each way) plus a source field and an
+                                         A0 field when given, however many steps the launch fuses;
+                                         with k0 = 1 and K2 = 1 the library moves phi and two or
+                                         three moments instead (btrt_get_sweep) */
     int64_t step;                     /* steps taken (btrt_get_info only) */
 } btrt_info_t;
 
@@ -229,16 +229,19 @@ int btrt_set_walls(btrt_t* h, const double* values, int64_t steps);
  *                     k >= 2 each wavefront walks a strip of 66 - 2k columns down the grid and
  *                     keeps the k - 1 intermediate time levels in registers, so the state is
  *                     read and written once per k steps. Step counts that are not a multiple of
- *                     k end with one shorter launch.
+ *                     k end with one shorter launch. The automatic choices named here are those
+ *                     btrt_get_launch reports: below 2^20 nodes an automatic shape advances several
+ *                     steps of one btrt_step call in each launch, and with k0 = 1 and K2 = 1 larger
+ *                     grids may take more steps than reported, on blocks and regions
+ *                     (btrt_get_sweep)
  *   strip_rows        rows per strip of the walkers (0: automatic, 8 .. 32 by grid size, up to
  *                     64 from six steps per launch on; FP64 walkers from six steps on, which
  *                     hold one wavefront per SIMD, take the height that fits every strip in
  *                     the resident slots at once when that is 64 rows or more);
  *                     with one step per launch, the tile height 1, 2, 4, 8 or 16 (0: 4)
- *                     With k0 = 1 and K2 = 1 in FP64/FP32 storage, automatic strips are cut so that
- *                     all of a launch are resident at once (reported as the next lower of 8, 16, 32
- *                     and 64 rows below 64), and an automatic shape of one step per launch advances
- *                     several of the steps of one btrt_step call in each launch
+ *                     With k0 = 1 and K2 = 1 automatic strips are cut so that all of a launch are
+ *                     resident at once (reported as the next lower of 8, 16, 32 and 64 rows below
+ *                     64)
  *   strips_per_group  1 or 4 strips per workgroup, walked side by side (0: auto)
  *   tile              1 with steps_per_launch 2: the two-step LDS tile kernel instead of a
  *                     strip walker (tiles of 64 x 8 nodes in FP64, 64 x 16 otherwise; with k0 = 1 and

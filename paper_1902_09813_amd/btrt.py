@@ -350,7 +350,7 @@ class Solver:
         return self
 
     def launch(self) -> tuple:
-        """(steps_per_launch, strip_rows, strips_per_group, tile) in force, resolved."""
+        """(steps_per_launch, strip_rows, strips_per_group, tile) in force, resolved; sweep() tells what runs."""
         cfg = Launch()
         _check(lib().btrt_get_launch(self.h, ctypes.byref(cfg)), "btrt_get_launch")
         return cfg.as_tuple()

@@ -15,10 +15,10 @@
 // A Dirichlet face (half-way bounce-back) replaces the part of a missing node; the sums over the five
 // links of a face close (mom3_walls), links through an edge of the box taking the mean of two faces.
 //
-// What bounds it: with one step per launch the words it moves (256^3 FP64, 1.07 GB in 243 us), with two
-// the issue of its instructions (about 134 per FP64 update and lane, and 8 of 20 lane-rows of a tile
-// halo). Measured per step, population form -> moment form: 256^3 nonlinear FP64 687 -> 205 us, FP32
-// 421 -> 103 us; 125^3 FP64 137 -> 33 us; 20^3 FP64 8.2 -> 5.2 us.
+// What bounds it: with one step per launch the words it moves (256^3 FP64, 1.07 GB in 243 us). With two,
+// FP32 the issue of its instructions (VALU busy 0.98), FP64 the waits that two wavefronts a SIMD leave open (0.53
+// busy at 2.03 GHz; 242 VALU lane-instructions per update, 0.63 of a tile kept). Measured per step, population
+// form -> moment form: 256^3 nonlinear FP64 687 -> 218 us, FP32 421 -> 110 us; 125^3 FP64 137 -> 33 us; 20^3 FP64 8.2 -> 5.2 us.
 //
 // State after n >= 1 steps: f+(n-1) as phi(n-1), q(n-1), g(n-1). At n = 0 the planes already hold f+(0)
 // (pointwise from phi0): the first step changes the step count alone.

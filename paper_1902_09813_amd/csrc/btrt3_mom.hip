@@ -45,8 +45,7 @@ __device__ __forceinline__ int wrap3(int v, int n)
 // plane z of the state from memory (loads issued a plane ahead); step l + 1 updates plane z - l - 1 as
 // soon as step l has plane z - l. x neighbours come by lane shifts, the rows beside a lane's own
 // through LDS (eight values per lane, level and plane; one barrier per level), planes from eight
-// values per column and level in registers. What bounds it: with one step per launch the nine words
-// of state it moves per node, with two the issue of its instructions (about 150 per FP64 update).
+// values per column and level in registers. (What bounds it: btrt3_mom.h.)
 //
 // The values of level l are written again only after every wavefront has read them: with K >= 2 the
 // barrier of another level lies between, with K = 1 the planes alternate between two buffers.
@@ -263,7 +262,8 @@ hipError_t mom3_launch(Sweep3<T> a, int zc, hipStream_t s)
 }
 
 // Tiles: one step per launch 64 x 8 columns (many small workgroups), two steps 64 x 16 with two rows
-// per lane (60 x 12 of them output). 256^3 FP64, us a step at the best chunk: two steps with 8
+// per lane (60 x 12 of them output). 256^3 FP64, us a step at the best chunk (with a reciprocal of two Newton
+// steps; the third and the fixup cost 6 us more): two steps with 8
 // wavefronts of two rows 205, 12 of one row 204, 16 of one row (spills) 429, 8 of one row 256; FP32: 103,
 // 16 of one row 121, 16 of two rows 119, 8 of four rows 116.
 constexpr int kNW = 8;

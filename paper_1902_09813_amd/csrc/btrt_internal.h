@@ -118,7 +118,7 @@ struct LaunchCfg {
     int rows = 0;   // strip walkers (steps >= 2): rows per strip (0: automatic)
     int group = 0;  // strip walkers: strips per workgroup, 1 or kWalkGroup (0: automatic)
     int tile = 0;   // 1: steps == 2 through the LDS tile kernel instead of a strip walker
-    // Set by resolve_launch for automatic shapes; not part of the public shape.
+    // Set by resolve_launch for automatic shapes; not part of the public shape (btrt_get_sweep reports them).
     int fuse = 0;       // time steps the launches take where they differ from `steps` (0: steps)
     int fit_rows = 0;   // moment walkers: rows per strip fitted to the resident wavefront slots (0: rows)
     int block = 0;      // threads per workgroup of the block kernels (0: none)

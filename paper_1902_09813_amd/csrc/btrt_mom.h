@@ -18,9 +18,12 @@
 // close (mom_walls). About 50 FP64 operations per update with K1 per node, against 81 in the
 // population form, and four lane shifts instead of six.
 //
-// What bounds it: on large grids the issue of FP64/FP32 instructions (63 VALU instructions per FP64
-// update and lane at seven steps, 114 in the population walker; three words of state move per node
-// and launch instead of ten). Measured per step, population form -> moment form: 4096^2 nonlinear
+// What bounds it: on large grids the issue of FP64/FP32 instructions (80 VALU lane-instructions per FP64
+// update at seven steps, halo and fill included, 131 in the population walker; three words of state move
+// per node and launch instead of ten). Counters at 4096^2: FP64 walkers VALU busy 0.80 of the cycles at a clock
+// held to 2.04 GHz (2.31 in the one-step kernel); FP32 regions an instruction every 3.1 cycles and SIMD. Short
+// strips are bound by their chain instead (1024^2 with walls FP64, 10 rows kept of 18: 0.35 to 0.45 busy), small
+// grids by launches (64^2 0.07). Measured per step, population form -> moment form: 4096^2 nonlinear
 // FP64 92 -> 47 us, FP32 57 -> 27 us (regions); 1024^2 with walls FP64 14.6 -> 5.7 us; 64^2 FP64 4.1 -> 0.73
 // us (blocks).
 //
@@ -900,7 +903,7 @@ LaunchCfg mom_resolve(const SweepArgs<T>& a, LaunchCfg cfg)
             }
         }
         // Above, the region kernel; FP64 only up to 2^20 nodes (2^21 periodic without an A0 field), above which
-        // both kernels run at what the card's power allows and the walkers issue less. us a step, walkers and
+        // the walkers, which issue fewer instructions an update, are the faster. us a step, walkers and
         // regions: FP32 hill 500^2 1.83 and 1.14, 1024^2 3.22 and 2.42, 2600 x 2200 11.9 and 10.5; with walls
         // and a source 500^2 3.20 and 1.47, 1700 x 900 5.4 and 4.9; FP64 hill 500^2 2.04 and 1.50, 1024^2 4.5
         // and 4.0, 1700 x 900 5.9 and 5.4, 2000^2 13.6 and 14.5; walls 500^2 3.9 and 2.3, 850 x 1200 6.0 and

@@ -66,8 +66,9 @@ __host__ __device__ __forceinline__ RegionSpan region_span(int t, int n, int siz
 // A workgroup of NW wavefronts owns 64 x (NW R) nodes, each lane one column of its wavefront's R rows in
 // registers, and takes `steps` steps on them; the valid part narrows by one node per open side and step.
 // x neighbours come by lane shifts and rows from the lane's own registers but for the first and last row
-// of a wavefront, whose sums (four values a lane) go through LDS, one barrier a step. Issue bounds it, as
-// it does the strip walkers; those fill 2 K rows per strip, which at the strip heights that fill the chip
+// of a wavefront, whose sums (four values a lane) go through LDS, one barrier a step. Where several regions
+// share a CU issue bounds it (4096^2 FP32: a VALU instruction every 3.1 cycles and SIMD), in a single round the
+// barrier's wait as well (1531 x 977 FP32: VALU busy 0.58 to 0.67). Strip walkers fill 2 K rows per strip, which at the strip heights that fill the chip
 // costs up to half of what they compute (1531 x 977, four steps: 14 rows of 22), and a region of six rows
 // a lane by 12 wavefronts keeps 0.68 (six steps). The four parts of each row's sums are independent, so a
 // wavefront also has more to issue than a walker's chain of levels.
