@@ -430,7 +430,8 @@ def traffic_for(precision_name, nodes, sweep):
 
 def valu_busy_for(precision_name, nodes, sweep):
     """Fraction of SIMD cycles with a VALU instruction in flight (SQ_ACTIVE_INST_VALU x 4 over
-    1024 SIMDs x GRBM_GUI_ACTIVE per XCD), or None if not measured for this shape and source."""
+    1024 SIMDs x GRBM_GUI_ACTIVE per XCD; FP32 instructions of several wavefronts overlap, which passes 1), or
+    None if not measured for this shape and source."""
     ent = counter_record(precision_name, nodes, sweep)
     return None if ent is None else ent.get("valu_busy")
 

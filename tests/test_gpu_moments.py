@@ -92,6 +92,23 @@ def test_initial_state_is_rounded_once(precision, u):
             assert np.all(np.abs(f[i] - feq) <= bound), (i, kw, precision)
 
 
+@pytest.mark.parametrize("precision", [btrt.F16DEV, btrt.BF16DEV])
+def test_16_bit_handles_keep_fp32_moments(precision):
+    # Nothing is rounded to 16 bits between steps: the bits of an FP32 handle, every time, whatever the memory held.
+    import torch
+
+    for j, w in enumerate(variants(131, 70, BCS["walls"])):
+        with btrt.Solver(btrt.problem_from_workload(w, precision=btrt.F32), w.phi0()) as s:
+            want = s.step(60).populations()
+        for fill in (0, 255, 66):
+            x = torch.full((1 << 26,), fill, dtype=torch.uint8, device="cuda")
+            torch.cuda.synchronize()
+            del x
+            torch.cuda.empty_cache()
+            with btrt.Solver(btrt.problem_from_workload(w, precision=precision), w.phi0()) as s:
+                assert np.array_equal(s.step(60).populations(), want), (j, fill)
+
+
 @pytest.mark.parametrize("size", [(97, 83), (400, 320)], ids=["blocks", "regions"])
 def test_periodic_shift_invariance(size):
     # A run from a shifted field (and source) gives the shifted populations: no kernel mixes a node's data with
